@@ -398,9 +398,9 @@ dg_status dg_rowsum(const dg_desc* d, const float* X, float* out, int64_t rows,
  * run (the paper's evaluation, Sec. 7: rmsnorm).
  *   X: device, rows x cols fp32 row-major;  w: device, cols bf16 or NULL;
  *   Y: device, rows x cols of out_dtype (written, never read; may not
- *   overlap X).  rows = 0 or cols = 0 is a no-op.  Uses a library-owned
- *   workspace of rows fp32 values per (device, stream) (DG_ERR_NOMEM if it
- *   cannot grow); two launches on `stream`.  Errors as dg_rowsum, plus
+ *   overlap X).  rows = 0 or cols = 0 is a no-op.  One launch, or two on
+ *   `stream` through a library-owned workspace of rows fp32 values per
+ *   (device, stream) (DG_ERR_NOMEM if it cannot grow).  Errors as dg_rowsum, plus
  *   DG_ERR_INVALID for a descriptor whose reduce_op is not DG_OP_SUMSQ. */
 dg_status dg_rmsnorm(const dg_desc* d, const float* X, const void* w, float eps, void* Y,
                      int64_t rows, int64_t cols, void* stream);
@@ -418,10 +418,10 @@ dg_status dg_rmsnorm(const dg_desc* d, const float* X, const void* w, float eps,
  * kernels (Sec. 7); the two sums are the order-sensitive steps.
  *   X: device, rows x cols fp32;  Y: device, rows x cols of out_dtype (may
  *   not overlap X).  rows = 0 or cols = 0 is a no-op.  One launch for
- *   strided lanes (64, 128 or 256) with rows of at most 8192 aligned
- *   elements; otherwise four launches through a library-owned workspace of
- *   rows x (cols + 2) fp32 values per (device, stream).  Errors as
- *   dg_rowsum. */
+ *   contiguous leaves of 64 with fma = 1 and for strided lanes (64, 128 or
+ *   256; 64 lanes past 65536 columns only below 512 rows); otherwise four
+ *   launches through a library-owned workspace of rows x (cols + 2) fp32
+ *   values per (device, stream).  Errors as dg_rowsum. */
 dg_status dg_layernorm(const dg_desc* d, const float* X, const void* w, const void* b, float eps,
                        void* Y, int64_t rows, int64_t cols, void* stream);
 
@@ -437,11 +437,12 @@ dg_status dg_layernorm(const dg_desc* d, const float* X, const void* w, const vo
  *   the only order-sensitive step.
  *   X: device, rows x cols fp32 row-major;  Y: device, rows x cols of
  *   out_dtype (written, never read; may not overlap X).  rows = 0 or
- *   cols = 0 is a no-op.  One launch when the descriptor has strided lanes
- *   (64, 128 or 256) and a row fits in registers (cols <= 8192, aligned);
- *   otherwise three launches through a library-owned workspace of
- *   rows x (cols + 1) fp32 values per (device, stream) (DG_ERR_NOMEM if it
- *   cannot grow).  Errors as dg_rowsum, plus DG_ERR_INVALID for a
+ *   cols = 0 is a no-op.  One launch when the descriptor has contiguous
+ *   leaves of 64 or strided lanes (64, 128 or 256); fewer than 256 rows of
+ *   65537 to 262144 columns over contiguous leaves take three launches and a
+ *   small workspace, any other descriptor three launches through a
+ *   library-owned workspace of rows x (cols + 1) fp32 values per (device,
+ *   stream) (DG_ERR_NOMEM if it cannot grow).  Errors as dg_rowsum, plus DG_ERR_INVALID for a
  *   descriptor whose reduce_op is not DG_OP_SUM. */
 dg_status dg_softmax(const dg_desc* d, const float* X, void* Y, int64_t rows, int64_t cols,
                      void* stream);

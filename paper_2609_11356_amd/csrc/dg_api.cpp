@@ -760,6 +760,17 @@ static dg::RowsumArgs rowsum_args(const dg_desc* d, const float* X, float* out, 
   return a;
 }
 
+// Whether a row sum spreads each row over the waves of a workgroup: rows too
+// few to fill the chip with one wave each (64 x 32768: 7.7 against 18.6 us;
+// at 2048 rows the one-wave kernels are level), or contiguous leaves whose
+// rows start off the one-wave kernel's vector loads (1 x 100001: 8.8 against
+// 224 us).
+static bool rowsum_over_waves(const dg::RowsumArgs& a) {
+  if (!dg::row_fused_ok(a, dg::ROW_SUM, a.rows, a.cols)) return false;
+  if (!a.strided && (a.cols % 4 || !aligned(a.X, 16))) return true;
+  return a.rows < 1024 && a.cols > 8192;
+}
+
 dg_status dg_rowsum(const dg_desc* d, const float* X, float* out, int64_t rows, int64_t cols,
                     void* stream) {
   if (!d) return DG_ERR_INVALID;
@@ -769,6 +780,15 @@ dg_status dg_rowsum(const dg_desc* d, const float* X, float* out, int64_t rows, 
   if (!aligned(out, 4) || (X && !aligned(X, 4))) return DG_ERR_ALIGN;
   if ((rows + 3) / 4 > (int64_t)0x7fffffff) return DG_ERR_SHAPE;
   dg::RowsumArgs a = rowsum_args(d, X, out, rows, cols);
+  if (rowsum_over_waves(a)) {
+    dg::NormArgs n;
+    std::memset(&n, 0, sizeof n);
+    n.X = X;
+    n.rows = rows;
+    n.cols = cols;
+    if (dg::launch_row_fused(a, n, dg::ROW_SUM, (hipStream_t)stream) != hipSuccess) return DG_ERR_HIP;
+    return DG_OK;
+  }
   if (dg::launch_rowsum(a, (hipStream_t)stream) != hipSuccess) return DG_ERR_HIP;
   return DG_OK;
 }
@@ -792,6 +812,17 @@ dg_status dg_softmax(const dg_desc* d, const float* X, void* Y, int64_t rows, in
   n.out_bf16 = out_bf16;
   if (dg::softmax_fused_ok(a, n)) {
     if (dg::launch_softmax_fused(a, n, st) != hipSuccess) return DG_ERR_HIP;
+    return DG_OK;
+  }
+  if (dg::softmax_split_ok(a, rows, cols)) {
+    void* ws = nullptr;
+    dg_status s = get_workspace(st, dg::softmax_split_bytes(rows, cols), &ws);
+    if (s != DG_OK) return s;
+    if (dg::launch_softmax_split(n, (float*)ws, st) != hipSuccess) return DG_ERR_HIP;
+    return DG_OK;
+  }
+  if (dg::row_fused_ok(a, dg::ROW_SMX, rows, cols)) {
+    if (dg::launch_row_fused(a, n, dg::ROW_SMX, st) != hipSuccess) return DG_ERR_HIP;
     return DG_OK;
   }
   // exponentials to the workspace, their reciprocal sums after them, then the products
@@ -839,6 +870,10 @@ dg_status dg_layernorm(const dg_desc* d, const float* X, const void* w, const vo
   n.pre_round = d->p.norm_round == DG_NORM_PRE_WEIGHT;
   if (dg::rmsnorm_fused_ok(a, n)) {
     if (dg::launch_layernorm_fused(a, n, st) != hipSuccess) return DG_ERR_HIP;
+    return DG_OK;
+  }
+  if (dg::row_fused_ok(a, dg::ROW_LN, rows, cols)) {
+    if (dg::launch_row_fused(a, n, dg::ROW_LN, st) != hipSuccess) return DG_ERR_HIP;
     return DG_OK;
   }
   // means, centred values, reciprocal roots, then the scaling
@@ -894,6 +929,10 @@ dg_status dg_rmsnorm(const dg_desc* d, const float* X, const void* w, float eps,
   // workspace and a scaling pass
   if (dg::rmsnorm_fused_ok(a, n)) {
     if (dg::launch_rmsnorm_fused(a, n, st) != hipSuccess) return DG_ERR_HIP;
+    return DG_OK;
+  }
+  if (dg::row_fused_ok(a, dg::ROW_RMS, rows, cols)) {
+    if (dg::launch_row_fused(a, n, dg::ROW_RMS, st) != hipSuccess) return DG_ERR_HIP;
     return DG_OK;
   }
   void* ws = nullptr;

@@ -150,6 +150,15 @@ hipError_t launch_softmax_exp(const NormArgs& a, hipStream_t s);
 // centred values into a.Y given the means in a.rinv (three-pass path)
 hipError_t launch_layernorm_fused(const RowsumArgs& r, const NormArgs& a, hipStream_t s);
 hipError_t launch_layernorm_center(const NormArgs& a, hipStream_t s);
+// one pass with the row in registers over the waves of a workgroup (dg_rownorm.hip):
+// rowsum into r.out, RMS norm, layer norm or softmax into a.Y (r.eps the norms' eps)
+enum { ROW_SUM = 0, ROW_RMS = 1, ROW_LN = 2, ROW_SMX = 3 };
+bool row_fused_ok(const RowsumArgs& r, int kind, int64_t rows, int64_t cols);
+hipError_t launch_row_fused(const RowsumArgs& r, const NormArgs& a, int kind, hipStream_t s);
+// softmax of few wide rows over many workgroups per row, through ws
+bool softmax_split_ok(const RowsumArgs& r, int64_t rows, int64_t cols);
+size_t softmax_split_bytes(int64_t rows, int64_t cols);
+hipError_t launch_softmax_split(const NormArgs& a, float* ws, hipStream_t s);
 // column sums of a GEMM output: subtrees of 256 rows, then their tree
 hipError_t launch_colsum(const ColsumArgs& a, hipStream_t s);
 hipError_t launch_colsum_merge(const ColsumArgs& a, hipStream_t s);   // run roots in a.part only
