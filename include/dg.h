@@ -291,6 +291,11 @@ dg_status dg_gemm_packed(const dg_desc* d, const void* A, const void* Bp, const 
 dg_status dg_gemm_colsum(const dg_desc* d, const void* A, const void* B, const void* bias,
                          void* C, float* colsum, int64_t M, int64_t N, int64_t K, void* stream);
 
+/* Sizes and alignment (dg_gemm): bf16 and binary16 operands run on the tiled
+ * kernels at any N, K >= 8, any part start and any element-aligned pointers;
+ * strided splits, scalar descriptors and a short leading tile off the chunk
+ * grid keep the kernels named below. */
+
 /* Speed knobs for dg_gemm_knobs.  Any value gives the same bits as
  * dg_gemm; they exist so that this can be checked.  0 = the library's
  * choice. */

@@ -478,15 +478,15 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
   bool tc_ok = gen && !scalar && !strided && !b8 && !f8 && (p.fma == 1 || d->group == 32) && p.tile_k % 32 == 0 &&
                K % 8 == 0 && N % 8 == 0 && aligned(A, 16) && aligned(B, 16) && aligned(C, 16) &&
                (!need_bias || aligned(bias, 16));
-  int64_t max_tiles = 0;
-  for (int s = 0; s < a.S && tc_ok; ++s) {
+  int64_t part_tiles = 0;   // the longest part's accumulator tiles
+  for (int s = 0; s < a.S; ++s) {
     const int64_t len = a.cuts[s + 1] - a.cuts[s];
     if (a.cuts[s] % 8 || (a.tail_first && (len % p.tile_k) % 32)) tc_ok = false;
-    max_tiles = std::max<int64_t>(max_tiles, (len + p.tile_k - 1) / p.tile_k);
+    part_tiles = std::max<int64_t>(part_tiles, (len + p.tile_k - 1) / p.tile_k);
   }
   int tc_levels = 2;
-  while (tc_levels < 7 && max_tiles > ((int64_t)1 << tc_levels)) ++tc_levels;
-  if (p.tile_combine == DG_TREE && max_tiles > 128) tc_ok = false;
+  while (tc_levels < 7 && part_tiles > ((int64_t)1 << tc_levels)) ++tc_levels;
+  if (p.tile_combine == DG_TREE && part_tiles > 128) tc_ok = false;
   if (scalar) {
     tiled_ok = false;
     kern = 9;
@@ -530,12 +530,42 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
     depth = c.depth;
     slab_k = c.slab_k;
   }
+  // Sizes, part starts or pointers off the 8-element grid: the same pipelines
+  // with chunks loaded where they lie (dg_gemm_odd.hip).  A short leading tile
+  // must still be whole chunks, because the chunk grid restarts after it, and
+  // the last chunk of each matrix must lie in its last row (N, K >= 8); the
+  // rest stays on the generic kernel.
+  bool odd = false;
+  if (kern == 0 && !f8 && !strided && N >= 8 && K >= 8) {
+    odd = true;
+    for (int s = 0; s < a.S; ++s) {
+      const int64_t len = a.cuts[s + 1] - a.cuts[s];
+      if (a.tail_first && (len % p.tile_k) % (gen ? 32 : 8)) odd = false;
+    }
+    if (gen) {
+      if (d->group != 32 && p.fma == 0) odd = false;
+      if (p.tile_k % 32 || (p.tile_combine == DG_TREE && (p.fma == 0 || part_tiles > 128))) odd = false;
+      if (((M + 127) / 128) * ((N + 63) / 64) > INT32_MAX) odd = false;
+      if (odd) kern = 12;
+    } else if (odd) {
+      AutoConfig c = auto_config(M, N, a.S);
+      if (c.kern == 5 && !pp_fits(a)) c = {3, 64, 128, 3, 2, 0, 0};
+      kern = c.kern;
+      tm = c.tm;
+      tn = c.tn;
+      order = c.order;
+      if (kern != 4 && ((M + tm - 1) / tm) * ((N + tn - 1) / tn) > INT32_MAX) return DG_ERR_SHAPE;
+    }
+  }
   if (colsum_part && a.S == 1 && (kern == 6 || (kern == 5 && tm == 256))) {
     a.colsum_part = colsum_part;
     *fused = true;
   }
   hipError_t e;
-  if (kern == 11) {
+  if (odd) {
+    a.order = kern == 12 ? 1 : order;
+    e = kern == 12 ? dg::launch_gemm_odd_tc(a, tc_levels, st) : dg::launch_gemm_odd(a, kern, tm, tn, st);
+  } else if (kern == 11) {
     e = dg::launch_gemm_panel(a, panel_tms, panel_depth, panel_avec, st);
   } else if (kern == 14) {
     if (((M + 255) / 256) * ((N + 127) / 128) > INT32_MAX) return DG_ERR_SHAPE;

@@ -117,6 +117,10 @@ hipError_t launch_gemm_f8(const GemmArgs& a, int tile, hipStream_t s);
 // loaded direct to LDS (the tiled layout's conditions; M K and K N below
 // 2^30 elements)
 hipError_t launch_gemm_b16n(const GemmArgs& a, hipStream_t s);
+// the few-row (4), v3 (3) and ping-pong (5) kernels, and the tile-combine one, on
+// operands of any size and alignment (N, K >= 8; contiguous parts)
+hipError_t launch_gemm_odd(const GemmArgs& a, int kern, int tile_m, int tile_n, hipStream_t s);
+hipError_t launch_gemm_odd_tc(const GemmArgs& a, int levels, hipStream_t s);
 hipError_t launch_gemm_wide(const GemmArgs& a, int tile_m, int tile_n, hipStream_t s);
 bool wide_supported(int tile_m, int tile_n);
 bool wide_is_pp(int tile_m, int tile_n);   // the ping-pong kernel (buffer-resource offsets)
