@@ -16,8 +16,9 @@
 // the block's keys from the block start, with alpha O as the accumulator
 // (pv_fma) or from +0 and then added.  The end: O / l, or O * (1 / l).
 //
-// Kernel: one wave per RW query rows (16 or 32: one or two 16-row MFMA
-// tiles), NW waves per workgroup (the rows of a workgroup share one causal
+// Two kernels: attn_fwd_t (below, tree row sums accumulated in place) and
+// attn_fwd, for the other orders and 16-row causal splits: one wave per RW
+// query rows (16 or 32: one or two 16-row MFMA tiles), NW waves per workgroup (the rows of a workgroup share one causal
 // split: BLOCK_M is a multiple of RW NW).  Each block's K and V rows are in
 // LDS (two buffers: the next block's rows are fetched into registers while
 // the current block computes and stored at its end, one barrier per block;
@@ -30,6 +31,8 @@
 // NST) are adds within a lane and the last four are DPP lane steps; P~ goes
 // through the wave's LDS area as [key][row] (four rows per 8-byte write) and
 // comes back in operand layout through the transposing LDS read.
+#include <type_traits>
+
 #include "dg_device.h"
 #include "dg_internal.h"
 #include "dg_lanes.h"
@@ -360,6 +363,349 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd(AttnArgs a) {
   }
 }
 
+// ------------------------------------------------ transposed score tiles
+//
+// The tree row sum with P V accumulated in place (pv_fma), RW = 32 or 16
+// query rows per wave on v_mfma_f32_32x32x16_bf16 or 16x16x32 (chunks of 8 k
+// either way, so the same bits).  The tiles are computed transposed --
+// S^T = K Q^T, O^T += V^T P~^T -- so that a lane owns one query row (l % RW;
+// G = l / RW names its share of the keys):
+//   * the maximum, the row sum and the rescale are in-lane work plus one
+//     (RW 32) or two exchanges between lane groups, and alpha is one
+//     exponential per row, not one per row and lane group;
+//   * the rows of a K tile are taken in an order (kmap) that leaves lane l
+//     with keys KS kk + 8 G + 0..7 of every KS-key step kk: exactly its
+//     operand of the P~ V instruction, so P~ never leaves the registers (the
+//     kernel above passes it through LDS);
+//   * with RW = 32 each K and V fragment read from LDS serves 32 rows.
+// The row-sum tree: 8 keys in the lane, the lane groups by v_permlane swaps,
+// then the steps' nodes in key order.
+//
+// Bound: VALU.  A score takes 16 instructions (scale, half a maximum,
+// subtract, twelve for 2^x, tree add, half a conversion) at four cycles a
+// wave.  So the products run under them: while step kk's exponentials are
+// computed, the matrix cores work on P~ V of step kk - 1 and on K Q^T of the
+// next block (K runs a block ahead of V in LDS), and a second workgroup per
+// CU fills what is left.
+//
+// The K and V rows of a key block go from memory straight into LDS
+// (buffer_load ... lds), a block ahead in a second pair of arrays; the arrays
+// are separate variables so that the compiler waits for a pair's loads only.
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+namespace {
+
+typedef __attribute__((address_space(3))) void* lds_void;
+
+// A workgroup barrier without the fence that would drain the loads in flight.
+__device__ __forceinline__ void barrier_nofence() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// s_waitcnt immediate for at most n outstanding vector-memory operations.
+constexpr int vmcnt_only(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
+
+__device__ __forceinline__ void mfma_to(floatx16& c, const shortx8& a, const shortx8& b) {
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ void mfma_to(floatx4& c, const shortx8& a, const shortx8& b) { c = mfma(a, b, c); }
+
+// (a, b) -> ([a.lo, b.lo], [a.hi, b.hi]) over the wave's 32-lane halves.
+__device__ __forceinline__ void halves_swap(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(int, a), __builtin_bit_cast(int, b), false, false);
+  a = __builtin_bit_cast(float, (int)r[0]);
+  b = __builtin_bit_cast(float, (int)r[1]);
+}
+// The same over the 16-lane rows of each half.
+__device__ __forceinline__ void rows_swap(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(int, a), __builtin_bit_cast(int, b), false, false);
+  a = __builtin_bit_cast(float, (int)r[0]);
+  b = __builtin_bit_cast(float, (int)r[1]);
+}
+
+// exp2_f32 for x <= 0, -inf or NaN (every score minus the running maximum):
+// the same steps and bits.  Only the lower clamp can be reached; as
+// v_maximum3 it lets a NaN through, which then passes every later step.
+__device__ __forceinline__ float exp2_nonpos(float x_in) {
+  float x;
+  asm("v_maximum3_f32 %0, %1, %2, %2" : "=v"(x) : "v"(x_in), "s"(-151.0f));
+  const float n = __builtin_rintf(x);
+  const float f = x - n;
+  float p = 0x1.ffcbfcp-17f;
+  p = __builtin_fmaf(p, f, 0x1.430912p-13f);
+  p = __builtin_fmaf(p, f, 0x1.5d87fep-10f);
+  p = __builtin_fmaf(p, f, 0x1.3b2ab6p-7f);
+  p = __builtin_fmaf(p, f, 0x1.c6b08ep-5f);
+  p = __builtin_fmaf(p, f, 0x1.ebfbep-3f);
+  p = __builtin_fmaf(p, f, 0x1.62e43p-1f);
+  p = __builtin_fmaf(p, f, 1.0f);
+  return __builtin_ldexpf(p, (int)n);
+}
+
+// Key of MFMA row r of a K tile, and the swizzle of the K and V rows in LDS
+// (chunk c of row t at c ^ swz(t)): the 16 rows one K fragment read takes, and
+// the rows a transposing V read takes, on distinct slots of a 256-byte window.
+template <int RW>
+__device__ __forceinline__ int key_of_row(int r) {
+  if constexpr (RW == 32) return 16 * (r >> 4) + 8 * ((r >> 2) & 1) + 4 * ((r >> 3) & 1) + (r & 3);
+  else return 8 * (r >> 2) + (r & 3);            // + 4 in the step's second tile
+}
+template <int RW, int DC>
+__device__ __forceinline__ int k_swz(int t) {
+  if constexpr (RW == 32) return DC == 16 ? (t & 15) : ((t >> 1) & 7);
+  else return DC == 16 ? ((t & 3) | ((t >> 1) & 12)) : (((t >> 1) & 1) | ((t >> 2) & 6));
+}
+template <int RW, int DC>
+__device__ __forceinline__ int v_swz(int t) {
+  if constexpr (RW == 32) return DC == 16 ? ((t & 3) << 2) : (((t >> 1) & 1) << 2);
+  else return DC == 16 ? (((t & 3) << 1) ^ (((t >> 3) & 1) << 3)) : ((t & 3) << 1);
+}
+
+}  // namespace
+
+template <int D, int W, int NW, int RW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W * D * RW > 64 * 128 * 32 ? 1 : 2))) void
+attn_fwd_t(AttnArgs a) {
+  constexpr int DC = D / 8, KS = RW == 32 ? 16 : 32;       // chunks of a row; keys per P V step
+  constexpr int NK = W / KS, NP = W * RW / 64;             // steps; scores per lane
+  constexpr int QKS = D / KS, ND = D / RW, NT = W / RW;    // head-dimension steps, O and S tiles
+  constexpr int TR = RW == 32 ? 16 : 4;                    // registers per tile
+  constexpr int NQ = NT * QKS;                             // score instructions per block
+  constexpr int NLD = W * DC / (64 * NW);                  // K (and V) loads per wave and block, 1 KB each
+  static_assert(W * DC % (64 * NW) == 0, "whole loads per wave");
+  typedef std::conditional_t<RW == 32, floatx16, floatx4> tile_t;
+  __shared__ __attribute__((aligned(1024))) uint16_t K0[W * D];
+  __shared__ __attribute__((aligned(1024))) uint16_t V0[W * D];
+  __shared__ __attribute__((aligned(1024))) uint16_t K1[W * D];
+  __shared__ __attribute__((aligned(1024))) uint16_t V1[W * D];
+
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & (RW - 1), G = lane / RW;
+  const int64_t h = blockIdx.x;
+  const int64_t qb = a.causal ? (int64_t)gridDim.y - 1 - blockIdx.y : blockIdx.y;
+  const int64_t r0 = qb * (RW * NW);
+  const int64_t row = r0 + RW * wave + li;       // the lane's query row
+  const uint16_t* Qh = a.Q + h * a.Lq * D;
+  // every byte offset within a head's K and V fits 31 bits (the host checks)
+  const int rec = (int)(a.Lk * D * 2);
+  const __amdgpu_buffer_rsrc_t rK = __builtin_amdgcn_make_buffer_rsrc((void*)(a.K + h * a.Lk * D), (short)0, rec, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rV = __builtin_amdgcn_make_buffer_rsrc((void*)(a.V + h * a.Lk * D), (short)0, rec, 0x00020000);
+
+  // the lane's fragment addresses (elements; tiles and key steps add constants,
+  // which leave the swizzles as they are)
+  const int kmap = key_of_row<RW>(li);
+  const int vi = lane & 15, vrow = (RW == 32 ? 8 * G : 8 * (lane >> 4)) + (vi >> 2);
+  const int vcol = (RW == 32 ? 16 * ((lane >> 4) & 1) : 0) + 4 * (vi & 3);
+  constexpr int CPS = KS / 8;                    // chunks per head-dimension step
+  int kad[QKS], vad[ND];
+#pragma unroll
+  for (int k = 0; k < QKS; ++k) kad[k] = 8 * (kmap * DC + ((CPS * k + G) ^ k_swz<RW, DC>(kmap)));
+#pragma unroll
+  for (int dt = 0; dt < ND; ++dt) vad[dt] = 8 * (vrow * DC + (((RW * dt + vcol) >> 3) ^ v_swz<RW, DC>(vrow))) + (vcol & 7);
+  // first key of tile T relative to the lane's kmap
+  auto tile_key = [](int T) { return RW == 32 ? 32 * T : 32 * (T >> 1) + 4 * (T & 1); };
+  // score register i of the lane: the key (relative to 8 G)
+  auto key_of = [](int i) { return KS * (i >> 3) + (i & 7); };
+
+  shortx8 qf[QKS];
+#pragma unroll
+  for (int k = 0; k < QKS; ++k)
+    qf[k] = row < a.Lq ? *(const shortx8*)&Qh[row * D + KS * k + 8 * G] : shortx8{0, 0, 0, 0, 0, 0, 0, 0};
+
+  float m = -__builtin_inff(), l = 0.f;
+  tile_t O[ND], Sn[NT];
+#pragma unroll
+  for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+    for (int i = 0; i < TR; ++i) O[dt][i] = 0.f;
+
+  int end1 = (int)a.Lk, q0 = 0, q1 = 0;
+  if (a.causal) {
+    q0 = (int)(r0 / a.q_block * a.q_block);
+    q1 = q0 + a.q_block < a.Lk ? q0 + a.q_block : (int)a.Lk;
+    end1 = q0;
+  }
+  const int nb1 = (end1 + W - 1) / W, nb = nb1 + (a.causal ? (q1 - q0 + W - 1) / W : 0);
+  auto bounds = [&](int b, int* kb, int* ke) {
+    const bool st2 = b >= nb1;
+    *kb = st2 ? q0 + (b - nb1) * W : b * W;
+    const int lim = st2 ? q1 : end1;
+    *ke = *kb + W < lim ? *kb + W : lim;
+  };
+  // load i of the wave fills LDS chunks 64 (NLD wave + i) + lane; the lane
+  // fetches the chunk that belongs there (rows past the block end: zeros)
+  auto fetch = [&](bool v, uint16_t* dst, int b) {
+    if (b >= nb) return;
+    int kb, ke;
+    bounds(b, &kb, &ke);
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int q = 64 * (NLD * wave + i) + lane, t = q / DC, c = (q % DC) ^ (v ? v_swz<RW, DC>(t) : k_swz<RW, DC>(t));
+      const uint32_t off = kb + t < ke ? (uint32_t)((t * DC + c) * 16) : 0x80000000u;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(v ? rV : rK, (lds_void)(dst + 512 * (NLD * wave + i)), 16, off,
+                                               kb * D * 2, 0, 0);
+    }
+  };
+  // score instruction u of a block: head-dimension step u % QKS of tile u / QKS
+  auto score = [&](const uint16_t* K_, int u) {
+    const int T = u / QKS, k = u % QKS;
+    if (k == 0)
+#pragma unroll
+      for (int i = 0; i < TR; ++i) Sn[T][i] = 0.f;
+    mfma_to(Sn[T], *(const shortx8*)&K_[kad[k] + tile_key(T) * D], qf[k]);
+  };
+
+  // One key block: its scores in Sn, its V rows in V_; the next block's K rows
+  // in Kn (whose scores are left in Sn; past the last block they are not used).
+  auto block = [&](int b, const uint16_t* V_, const uint16_t* Kn) {
+    int kb, ke;
+    bounds(b, &kb, &ke);
+    const bool masked = b >= nb1;
+    float S[NP];
+#pragma unroll
+    for (int T = 0; T < NT; ++T)
+#pragma unroll
+      for (int i = 0; i < TR; ++i) S[TR * T + i] = Sn[T][i] * a.qk_scale;
+    // positions past the block end drop out (-inf), masked keys get -1e6
+    if (masked || ke - kb < W) {
+      const int left = ke - kb - 8 * G, diag = masked ? (int)row - kb - 8 * G : W;
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        float v = S[i];
+        if (key_of(i) >= left) v = -__builtin_inff();
+        else if (key_of(i) > diag) v = v + -1.0e6f;
+        S[i] = v;
+      }
+    }
+    float bm = S[0];
+#pragma unroll
+    for (int i = 1; i < NP; ++i) bm = __builtin_fmaxf(bm, S[i]);
+    float bo = bm;
+    if constexpr (RW == 16) {
+      rows_swap(bm, bo);
+      bm = __builtin_fmaxf(bm, bo);
+      bo = bm;
+    }
+    halves_swap(bm, bo);
+    const float mn = __builtin_fmaxf(m, __builtin_fmaxf(bm, bo));
+    const float alpha = exp2_nonpos(m - mn);
+    m = mn;
+    // rescale the output rows (skipped when every row of the wave keeps its
+    // maximum: alpha = 1 and 1 x O = O exactly)
+    if (__builtin_amdgcn_ballot_w64(!(alpha == 1.0f)) != 0) {
+#pragma unroll
+      for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+        for (int i = 0; i < TR; ++i) O[dt][i] = alpha * O[dt][i];
+    }
+    float n8[NK];
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) {
+      __builtin_amdgcn_sched_barrier(0);
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = exp2_nonpos(S[8 * kk + e] - mn);
+      // P~ = p narrowed to bf16, already in operand layout
+      u32x4 w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = f32x2_bf16x2(v[2 * e], v[2 * e + 1]);
+      const shortx8 pf = __builtin_bit_cast(shortx8, w);
+      // the perfect tree over the block's keys in order
+#pragma unroll
+      for (int x = 1; x < 8; x <<= 1)
+#pragma unroll
+        for (int e = 0; e < 8; e += 2 * x) v[e] = v[e] + v[e + x];
+      n8[kk] = v[0];
+      // the next block's scores, then O^T = alpha O^T (+) V^T P~^T: for each
+      // output the steps of KS keys in increasing order
+#pragma unroll
+      for (int u = kk * NQ / NK; u < (kk + 1) * NQ / NK; ++u) score(Kn, u);
+#pragma unroll
+      for (int dt = 0; dt < ND; ++dt) {
+        const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(&V_[vad[dt] + KS * kk * D]));
+        const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(&V_[vad[dt] + (KS * kk + 4) * D]));
+        mfma_to(O[dt], shortx8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]}, pf);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (RW == 32) {
+      // one swap turns two values spread over the halves into their two sums:
+      // 2^j values -> 2^(j-1) registers (one per half), down to the root
+#pragma unroll
+      for (int c = NK; c > 1; c >>= 1)
+#pragma unroll
+        for (int e = 0; e < c / 2; ++e) {
+          float x = n8[2 * e], y = n8[2 * e + 1];
+          halves_swap(x, y);
+          n8[e] = x + y;
+        }
+      float y = n8[0];
+      halves_swap(n8[0], y);
+      n8[0] = n8[0] + y;
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < NK; ++kk) {
+        float y = n8[kk];
+        rows_swap(n8[kk], y);
+        n8[kk] = n8[kk] + y;
+        y = n8[kk];
+        halves_swap(n8[kk], y);
+        n8[kk] = n8[kk] + y;
+      }
+#pragma unroll
+      for (int x = 1; x < NK; x <<= 1)
+#pragma unroll
+        for (int kk = 0; kk < NK; kk += 2 * x) n8[kk] = n8[kk] + n8[kk + x];
+    }
+    l = a.l_fma ? __builtin_fmaf(alpha, l, n8[0]) : alpha * l + n8[0];
+  };
+
+  // A wave's own loads have landed once its count is zero; after the barrier
+  // that follows, everybody's have, and the K pair of block b and the V pair of
+  // block b - 1 are free for the loads of blocks b + 2 and b + 1.
+  auto turn = [&]() {
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+    barrier_nofence();
+  };
+  fetch(false, K0, 0);
+  fetch(true, V0, 0);
+  turn();
+  fetch(false, K1, 1);
+#pragma unroll
+  for (int u = 0; u < NQ; ++u) score(K0, u);
+  for (int b = 0; b < nb; b += 2) {
+    turn();
+    fetch(false, K0, b + 2);
+    fetch(true, V1, b + 1);
+    block(b, V0, K1);
+    turn();
+    fetch(false, K1, b + 3);
+    fetch(true, V0, b + 2);
+    if (b + 1 < nb) block(b + 1, V1, K0);
+  }
+
+  // the final division (or reciprocal and products), then the output type;
+  // register i of tile dt holds column RW dt + 8 (i / 4) + 4 G + i % 4 (RW 32)
+  // or 16 dt + 4 G + i (RW 16)
+  if (row >= a.Lq) return;
+  const float r = 1.0f / l;
+#pragma unroll
+  for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+    for (int c = 0; c < TR / 4; ++c) {
+      float y[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y[e] = a.final_recip ? O[dt][4 * c + e] * r : O[dt][4 * c + e] / l;
+      const int64_t o = (h * a.Lq + row) * D + RW * dt + 8 * c + 4 * G;
+      if (a.out_bf16) *(uint2*)&((uint16_t*)a.O)[o] = uint2{f32x2_bf16x2(y[0], y[1]), f32x2_bf16x2(y[2], y[3])};
+      else *(float4*)&((float*)a.O)[o] = float4{y[0], y[1], y[2], y[3]};
+    }
+}
+
 namespace {
 
 template <int D, int W, int NW, int RW, bool PF>
@@ -377,14 +723,35 @@ hipError_t launch_one(const AttnArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Workgroup shape (speed only): 16-row waves (registers), eight of them
-// with the next block prefetched into a second buffer when the causal split
-// allows 128-row workgroups (four when it allows 64), else fewer waves
-// loading each block as it comes.  Measured on MI355X at 32 x 4096 x 128:
-// eight 16-row waves 357 TFLOP/s against 268 for four 32-row waves.
+template <int D, int W, int NW, int RW>
+hipError_t launch_t(const AttnArgs& a, hipStream_t st) {
+  constexpr int rows = RW * NW;
+  dim3 grid((unsigned)a.H, (unsigned)((a.Lq + rows - 1) / rows));
+  hipLaunchKernelGGL((attn_fwd_t<D, W, NW, RW>), grid, dim3(64 * NW), 0, st, a);
+  return hipGetLastError();
+}
+
+// Workgroup shape of attn_fwd (speed only): 16-row waves (registers), eight of
+// them with the next block prefetched into a second buffer when the causal
+// split allows 128-row workgroups (four when it allows 64), else fewer waves
+// loading each block as it comes.
+// Measured on MI355X, attn_fwd -> attn_fwd_t: 32 heads x 4096 x 128, blocks of
+// 64, 653 -> 383 us unmasked (717 TFLOP/s; 86 % of the VALU's cycles while a
+// CU is busy), 349 -> 219 us causal; blocks of 32 453 -> 247, of 128 401 -> 284
+// (causal); d = 64 219 -> 150; 16 heads x 1000 x 128 causal, 16-row waves, 41 ->
+// 26 (32-row waves: 45).
 template <int D, int W>
 hipError_t launch_dw(const AttnArgs& a, hipStream_t st) {
   const int64_t bm = a.causal ? a.q_block : 128;
+  // tree row sums accumulated in place (a head's K and V within 31-bit
+  // offsets): 32-row waves once they fill the chip's 1024 SIMDs, else 16-row
+  // ones, whose blocks take half the time
+  if (a.block_tree && a.pv_fma && a.Lk * D * 2 <= 0x7fffffff) {
+    const bool full = a.H * ((a.Lq + 31) / 32) >= 1024;
+    if (bm % 128 == 0 && full) return launch_t<D, W, 4, 32>(a, st);
+    if (bm % 64 == 0) return launch_t<D, W, 4, 16>(a, st);
+    if (bm % 32 == 0) return launch_t<D, W, 2, 16>(a, st);
+  }
   if constexpr (W == 128) {
     if (bm % 64 == 0) return launch_one<D, W, 4, 16, false>(a, st);
     return launch_one<D, W, 1, 16, false>(a, st);

@@ -1,0 +1,59 @@
+"""GPU parity of the attention kernels on transposed score tiles (tree row
+sums accumulated in place) against the CPU oracle, bit for bit: 32-row waves
+(heads enough to fill the chip; the first heads compared), 16-row waves, their
+row and key edges, and scores that are -inf or NaN."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2609_11356_amd import inputs
+from tests.gpu_util import assert_bits_equal
+from tests.test_gpu_attention import qkv, run, scale
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dg():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_11356_amd import dg as _dg
+    _dg.lib()
+    return _dg
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("w", [32, 64, 128])
+@pytest.mark.parametrize("shape", [(260, 128, 128, 128), (128, 257, 257, 128), (64, 513, 513, 256), (1024, 1, 97, 0),
+                                   (512, 33, 193, 0), (3, 47, 129, 0), (2, 191, 191, 32), (2, 130, 130, 64)])
+def test_tiles(dg, d, w, shape):
+    H, Lq, Lk, q_block = shape
+    desc = dict(key_block=w, causal=int(q_block > 0), q_block=q_block or 1, block_sum="tree", pv_fma=1,
+                l_fma=(w // 32) % 2, final="recip" if d == 64 else "div", out="bf16" if w == 64 else "f32")
+    Q, K, V = qkv(w + Lq, H, Lq, Lk, d, spread_v=w == 32)
+    print("attention", desc, shape, d, flush=True)
+    got = run(dg, desc, Q, K, V, scale(d))
+    n = 2
+    assert_bits_equal(got[:n], oracle.attention(desc, Q[:n], K[:n], V[:n], scale(d)), "%s %s d %d" % (desc, shape, d))
+    # heads are independent: the last one again, alone in a call (16-row waves)
+    assert np.array_equal(run(dg, desc, Q[-1:], K[-1:], V[-1:], scale(d))[0], got[-1])
+
+
+@pytest.mark.parametrize("H,causal", [(4, 0), (4, 1), (600, 0), (600, 1)])
+def test_tiles_special_scores(dg, H, causal):
+    """Keys whose scores overflow to -inf (probability zero), a row of -inf
+    only, NaN scores, and infinities in V under a zero probability: the
+    oracle's steps, NaN as a class."""
+    d, L = 64, 70
+    Q, K, V = qkv(5, H, L, L, d)
+    Q[:, :, 0] = 0x7F00                   # 1.7e38
+    K[:, :, 0] = 0x0000
+    K[:, 3, 0] = 0xC000                   # score -inf for every query
+    K[0, :, 0] = 0xC000                   # head 0: every score -inf
+    K[1, 9, 1] = 0x7FC0                   # head 1: one NaN key
+    V[2, 3, 5] = 0x7F80                   # head 2: inf where the probability is 0
+    desc = dict(key_block=32, causal=causal, q_block=64, block_sum="tree", out="f32")
+    got = run(dg, desc, Q, K, V, scale(d))
+    assert_bits_equal(got[:4], oracle.attention(desc, Q[:4], K[:4], V[:4], scale(d)), "special scores, %d heads" % H)
+    assert np.isnan(got[0]).all() and np.isfinite(got[3]).all()
