@@ -515,8 +515,10 @@ void dg_attn_desc_destroy(dg_attn_desc* d);
  *   and 1 / sqrt(d) into it).
  * H = 0 or Lq = 0 is a no-op.  DG_ERR_SHAPE for Lk < 1, H > 65535,
  * Lq > 16 * 65535, or a causal descriptor with Lq != Lk; DG_ERR_UNSUPPORTED for another d;
- * DG_ERR_ALIGN for a pointer not 16-byte aligned.  One launch on stream; no
- * workspace. */
+ * DG_ERR_ALIGN for a pointer not 16-byte aligned.  One launch on stream; for
+ * few query rows over many keys three launches through the library-owned
+ * workspace of the (device, stream) (never while the stream is captured, and
+ * one launch again if the workspace cannot grow). */
 dg_status dg_attention(const dg_attn_desc* d, const void* Q, const void* K, const void* V, void* O,
                        int64_t H, int64_t Lq, int64_t Lk, int64_t dim, float qk_scale, void* stream);
 

@@ -93,31 +93,53 @@ constexpr int F8_AUTO_TN = 128;
 struct Workspace {
   void* ptr = nullptr;
   size_t bytes = 0;
+  std::recursive_mutex mu;   // held by the call whose launches use ptr
 };
-std::mutex g_ws_mutex;
+std::mutex g_ws_mutex;       // the map
 std::map<std::pair<int, hipStream_t>, Workspace> g_ws;
+
+// A call's hold on its workspace: until the lease ends (the call has enqueued
+// all of its launches) no other host thread gets the same stream's workspace,
+// so the launches of two calls on one stream cannot interleave over it.
+typedef std::unique_lock<std::recursive_mutex> Lease;
 
 // Workspace of at least `bytes` owned by (current device, stream).  Growth is
 // stream-ordered (hipMallocAsync / hipFreeAsync on that stream), so launches
 // already enqueued on the stream keep their buffer until they finish.
-dg_status get_workspace(hipStream_t st, size_t bytes, void** out) {
+dg_status get_workspace(hipStream_t st, size_t bytes, void** out, Lease* lease) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return DG_ERR_HIP;
-  std::lock_guard<std::mutex> lock(g_ws_mutex);
-  Workspace& w = g_ws[{dev, st}];
-  if (w.bytes < bytes) {
+  Workspace* w;
+  {
+    std::lock_guard<std::mutex> lock(g_ws_mutex);
+    w = &g_ws[{dev, st}];    // a map node never moves
+  }
+  *lease = Lease(w->mu);
+  if (w->bytes < bytes) {
     size_t want = bytes + bytes / 4;
     void* p = nullptr;
     if (hipMallocAsync(&p, want, st) != hipSuccess) {
       (void)hipGetLastError();
       return DG_ERR_NOMEM;
     }
-    if (w.ptr) (void)hipFreeAsync(w.ptr, st);
-    w.ptr = p;
-    w.bytes = want;
+    if (w->ptr) (void)hipFreeAsync(w->ptr, st);
+    w->ptr = p;
+    w->bytes = want;
   }
-  *out = w.ptr;
+  *out = w->ptr;
   return DG_OK;
+}
+
+// Whether work enqueued on the stream is being captured into a graph (or the
+// runtime cannot say).  Attention takes no workspace then: it used none
+// before the split path, and a captured pointer would outlive the buffer.
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusActive;
+  if (hipStreamIsCapturing(st, &c) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return c != hipStreamCaptureStatusNone;
 }
 
 // Tile shape for the tiled kernel: a speed choice only.
@@ -446,6 +468,7 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
     }
   }
   hipStream_t st = (hipStream_t)stream;
+  Lease lease;
   if (a.S > 1) {
     void* ws = nullptr;
     const size_t bytes = (size_t)a.S * (size_t)M * (size_t)N * sizeof(float);
@@ -455,7 +478,7 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
         return DG_ERR_SCRATCH;
       if (dg::noalloc_scratch(&ws) != hipSuccess) return DG_ERR_HIP;
     } else {
-      dg_status s = get_workspace(st, bytes, &ws);
+      dg_status s = get_workspace(st, bytes, &ws, &lease);
       if (s != DG_OK) return s;
     }
     a.ws = (float*)ws;
@@ -748,11 +771,12 @@ dg_status dg_gemm_colsum(const dg_desc* d, const void* A, const void* B, const v
   // One part: the GEMM's epilogue may fold the 256-row runs itself (run roots
   // straight into colsum when there is one run); the workspace is free then.
   bool fused = false;
+  Lease lease;
   dg_status s;
   if (d->p.split_k == 1 && M > 0 && N > 0) {
     if (nrun > 1) {
       void* ws = nullptr;
-      s = get_workspace(st, (size_t)nrun * (size_t)N * sizeof(float), &ws);
+      s = get_workspace(st, (size_t)nrun * (size_t)N * sizeof(float), &ws, &lease);
       if (s != DG_OK) return s;
       c.part = (float*)ws;
     }
@@ -767,7 +791,7 @@ dg_status dg_gemm_colsum(const dg_desc* d, const void* A, const void* B, const v
   }
   if (nrun > 1 && !c.part) {
     void* ws = nullptr;
-    s = get_workspace(st, (size_t)nrun * (size_t)N * sizeof(float), &ws);
+    s = get_workspace(st, (size_t)nrun * (size_t)N * sizeof(float), &ws, &lease);
     if (s != DG_OK) return s;
     c.part = (float*)ws;
   }
@@ -846,7 +870,8 @@ dg_status dg_softmax(const dg_desc* d, const float* X, void* Y, int64_t rows, in
   }
   if (dg::softmax_split_ok(a, rows, cols)) {
     void* ws = nullptr;
-    dg_status s = get_workspace(st, dg::softmax_split_bytes(rows, cols), &ws);
+    Lease lease;
+    dg_status s = get_workspace(st, dg::softmax_split_bytes(rows, cols), &ws, &lease);
     if (s != DG_OK) return s;
     if (dg::launch_softmax_split(n, (float*)ws, st) != hipSuccess) return DG_ERR_HIP;
     return DG_OK;
@@ -857,7 +882,8 @@ dg_status dg_softmax(const dg_desc* d, const float* X, void* Y, int64_t rows, in
   }
   // exponentials to the workspace, their reciprocal sums after them, then the products
   void* ws = nullptr;
-  dg_status s = get_workspace(st, (size_t)rows * (size_t)(cols + 1) * sizeof(float), &ws);
+  Lease lease;
+  dg_status s = get_workspace(st, (size_t)rows * (size_t)(cols + 1) * sizeof(float), &ws, &lease);
   if (s != DG_OK) return s;
   float* E = (float*)ws;
   float* rinv = E + rows * cols;
@@ -908,7 +934,8 @@ dg_status dg_layernorm(const dg_desc* d, const float* X, const void* w, const vo
   }
   // means, centred values, reciprocal roots, then the scaling
   void* ws = nullptr;
-  dg_status s = get_workspace(st, (size_t)rows * (size_t)(cols + 2) * sizeof(float), &ws);
+  Lease lease;
+  dg_status s = get_workspace(st, (size_t)rows * (size_t)(cols + 2) * sizeof(float), &ws, &lease);
   if (s != DG_OK) return s;
   float* D = (float*)ws;
   float* mean = D + rows * cols;
@@ -966,7 +993,8 @@ dg_status dg_rmsnorm(const dg_desc* d, const float* X, const void* w, float eps,
     return DG_OK;
   }
   void* ws = nullptr;
-  dg_status s = get_workspace(st, (size_t)rows * sizeof(float), &ws);
+  Lease lease;
+  dg_status s = get_workspace(st, (size_t)rows * sizeof(float), &ws, &lease);
   if (s != DG_OK) return s;
   a.out = (float*)ws;
   n.rinv = (const float*)ws;
@@ -1026,7 +1054,17 @@ dg_status dg_attention(const dg_attn_desc* d, const void* Q, const void* K, cons
   a.l_fma = d->p.l_fma;
   a.final_recip = d->p.final_div == DG_ATTN_RECIP;
   a.out_bf16 = d->p.out_dtype == DG_BF16;
-  if (dg::launch_attention(a, dim, d->p.key_block, (hipStream_t)stream) != hipSuccess) return DG_ERR_HIP;
+  hipStream_t st = (hipStream_t)stream;
+  if (dg::attn_split_ok(a, dim, d->p.key_block) && !capturing(st)) {
+    // the blocks over the chip; without memory for the records, one launch
+    void* ws = nullptr;
+    Lease lease;
+    if (get_workspace(st, dg::attn_split_bytes(a, d->p.key_block), &ws, &lease) == DG_OK) {
+      if (dg::launch_attention_split(a, dim, d->p.key_block, (float*)ws, st) != hipSuccess) return DG_ERR_HIP;
+      return DG_OK;
+    }
+  }
+  if (dg::launch_attention(a, dim, d->p.key_block, st) != hipSuccess) return DG_ERR_HIP;
   return DG_OK;
 }
 

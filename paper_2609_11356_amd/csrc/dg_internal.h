@@ -93,6 +93,11 @@ struct AttnArgs {
 bool attn_supported(int64_t d, int key_block);
 hipError_t launch_attention(const AttnArgs& a, int64_t d, int key_block, hipStream_t s);
 
+// few query rows: the key blocks over the chip, in three launches through ws
+bool attn_split_ok(const AttnArgs& a, int64_t d, int key_block);
+size_t attn_split_bytes(const AttnArgs& a, int key_block);
+hipError_t launch_attention_split(const AttnArgs& a, int64_t d, int key_block, float* ws, hipStream_t s);
+
 // This device's copy of the fixed split-K scratch array of dg_gemm_noalloc
 // (DG_NOALLOC_SCRATCH_BYTES), looked up once per device with that device
 // current; never allocates.

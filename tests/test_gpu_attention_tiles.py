@@ -57,3 +57,74 @@ def test_tiles_special_scores(dg, H, causal):
     got = run(dg, desc, Q, K, V, scale(d))
     assert_bits_equal(got[:4], oracle.attention(desc, Q[:4], K[:4], V[:4], scale(d)), "special scores, %d heads" % H)
     assert np.isnan(got[0]).all() and np.isfinite(got[3]).all()
+
+
+# few rows over many keys (the split path): one and several 16-row tiles, odd
+# and short last blocks, the ring's remainders, causal walks cut at 16 .. 128
+SPLIT = [(1, 1, 769, 0), (3, 17, 1100, 0), (2, 5, 1024 + 31, 0), (1, 33, 2049, 0), (1, 1030, 1030, 16), (1, 1025, 1025, 128),
+         (2, 800, 800, 64)]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("w", [32, 64, 128])
+@pytest.mark.parametrize("shape", SPLIT)
+def test_split(dg, d, w, shape):
+    H, Lq, Lk, q_block = shape
+    desc = dict(key_block=w, causal=int(q_block > 0), q_block=q_block or 1, block_sum="tree", pv_fma=1,
+                l_fma=(w // 32) % 2, final="recip" if d == 64 else "div", out="bf16" if w == 64 else "f32")
+    Q, K, V = qkv(w + Lq, H, Lq, Lk, d, spread_v=w == 32)
+    print("attention", desc, shape, d, flush=True)
+    got = run(dg, desc, Q, K, V, scale(d))
+    if Lq <= 64:
+        assert_bits_equal(got, oracle.attention(desc, Q, K, V, scale(d)), "%s %s d %d" % (desc, shape, d))
+        return
+    ii = np.unique(np.concatenate([np.arange(0, Lq, 37), [0, 1, 15, 16, Lq // 2, Lq - 2, Lq - 1]]))
+    want = oracle.attention_rows(desc, Q, K, V, scale(d), np.zeros(len(ii), dtype=np.int64), ii)
+    rows = got[0][ii]
+    rows = (rows.astype(np.uint32) << 16).view(np.float32) if rows.dtype == np.uint16 else rows
+    assert_bits_equal(rows, want, "%s %s d %d" % (desc, shape, d))
+
+
+def test_split_special_scores(dg):
+    """-inf and NaN scores, an all -inf row, infinities in V at probability
+    zero and in the block cut short by the causal split."""
+    d, L = 64, 1100
+    Q, K, V = qkv(9, 4, 3, L, d)
+    Q[:, :, 0] = 0x7F00
+    K[:, :, 0] = 0x0000
+    K[:, 3, 0] = 0xC000
+    K[0, :, 0] = 0xC000
+    K[1, 900, 1] = 0x7FC0
+    V[2, 3, 5] = 0x7F80
+    desc = dict(key_block=64, block_sum="tree", out="f32")
+    assert_bits_equal(run(dg, desc, Q, K, V, scale(d)), oracle.attention(desc, Q, K, V, scale(d)), "special scores")
+    # causal: stage 1 of rows 48 .. 63 ends at key 48, inside a 64-key block
+    # whose later V rows are infinite and must not be read into its products
+    Q, K, V = qkv(11, 1, 1100, 1100, d)
+    V[0, 48:, 7] = 0x7F80
+    desc = dict(key_block=64, causal=1, q_block=48, block_sum="tree", out="f32")
+    ii = np.array([0, 16, 33, 47])
+    got = run(dg, desc, Q, K, V, scale(d))
+    assert_bits_equal(got[0][ii], oracle.attention_rows(desc, Q, K, V, scale(d), np.zeros(4, dtype=np.int64), ii), "cut stage")
+
+
+def test_few_rows_under_capture(dg):
+    """A captured call takes no workspace and replays to the eager bits."""
+    import torch
+    from tests.gpu_util import dev_bf16
+    Q, K, V = (dev_bf16(x) for x in qkv(3, 2, 4, 1500, 128))
+    desc = dg.AttnDesc(key_block=64)
+    want = torch.empty(Q.shape, dtype=torch.bfloat16, device="cuda")
+    dg.dg_attention(desc, Q, K, V, want, scale(128))
+    got = torch.zeros_like(want)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        dg.dg_attention(desc, Q, K, V, got, scale(128))
+    for _ in range(3):
+        got.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+        dg.dg_attention(desc, Q, K, V, want, scale(128))
+        torch.cuda.synchronize()
