@@ -150,6 +150,7 @@ class Desc:
         f = dict(self.DEFAULTS)
         f.update({k: v for k, v in fields.items() if k != "model"})
         self.fields = f
+        self.types = None
         p = dg_desc_params()
         p.struct_size = ctypes.sizeof(dg_desc_params)
         p.mma = MMA[f["mma"]]
@@ -202,11 +203,35 @@ def dg_desc_create(**fields) -> Desc:
     return Desc(**fields)
 
 
+# torch's names that every call needs, looked up once (torch is imported when
+# the library is loaded, not with this module)
+_tensor = _raw_stream = _get_device = _bf16 = _f32 = None
+
+
+def _bind_torch():
+    global _tensor, _raw_stream, _get_device, _bf16, _f32
+    import torch
+    _bf16, _f32 = torch.bfloat16, torch.float32
+    _get_device = torch.cuda.current_device
+    # the current stream's handle without building a Stream object (0.1 us
+    # instead of 3); the public way where this torch does not have it
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+        lambda device: torch.cuda.current_stream(device).cuda_stream)
+    _tensor = torch.Tensor
+
+
 def _stream(stream):
     if stream is not None:
         return int(stream)
-    import torch
-    return int(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None:
+        _bind_torch()
+    return _raw_stream(_get_device())
+
+
+def _is_tensor(x):
+    if _tensor is None:
+        _bind_torch()
+    return isinstance(x, _tensor)
 
 
 def _ptr(t):
@@ -247,8 +272,31 @@ def _in_dtypes(desc):
     return (torch.bfloat16,), (torch.bfloat16,)
 
 
+def _types(desc):
+    """(A dtypes, B dtypes, output dtype, bias needed) of a descriptor, kept on it."""
+    t = desc.types
+    if t is None:
+        a, b = _in_dtypes(desc)
+        t = desc.types = (a, b, _out_dtype(desc), desc.fields["epilogue"] != "none")
+    return t
+
+
 def _check_gemm(desc, A, B, bias, C):
     """Shapes, dtypes and layout of a GEMM call; returns (M, N, K)."""
+    want_a, want_b, want_c, need_bias = _types(desc)
+    sa, sb, sc = A.shape, B.shape, C.shape
+    # the usual call in one expression; anything else is named below
+    if (len(sa) == 2 and len(sb) == 2 and len(sc) == 2 and sa[1] == sb[0] and sc[0] == sa[0] and sc[1] == sb[1]
+            and A.dtype in want_a and B.dtype in want_b and C.dtype is want_c
+            and A.is_contiguous() and B.is_contiguous() and C.is_contiguous()
+            and A.is_cuda and B.is_cuda and C.is_cuda
+            and (not need_bias if bias is None else
+                 bias.dtype is _bf16 and bias.numel() == sb[1] and bias.is_contiguous() and bias.is_cuda)):
+        return sa[0], sb[1], sa[1]
+    return _check_gemm_named(desc, A, B, bias, C)
+
+
+def _check_gemm_named(desc, A, B, bias, C):
     import torch
     want_a, want_b = _in_dtypes(desc)
     _need(A.dtype in want_a and B.dtype in want_b, "A must be %s and B %s" % (want_a[0], want_b[0]))
@@ -271,6 +319,16 @@ def _check_gemm(desc, A, B, bias, C):
 def _check_rows(desc, X, Y, *vecs):
     """An fp32 row-major X, a Y of X's shape and the descriptor's output type,
     and optional bf16 per-column vectors; returns (rows, cols)."""
+    shape = X.shape
+    if (len(shape) == 2 and Y.shape == shape and X.dtype is _f32 and Y.dtype is _types(desc)[2]
+            and X.is_contiguous() and Y.is_contiguous() and X.is_cuda and Y.is_cuda
+            and all(t is None or (t.dtype is _bf16 and t.is_contiguous() and t.numel() == shape[1] and t.is_cuda)
+                    for t in vecs)):
+        return shape
+    return _check_rows_named(desc, X, Y, *vecs)
+
+
+def _check_rows_named(desc, X, Y, *vecs):
     import torch
     _need(X.dtype == torch.float32 and X.dim() == 2, "X must be an fp32 matrix")
     _need(tuple(Y.shape) == tuple(X.shape), "Y must have X's shape")
@@ -289,8 +347,7 @@ def dg_gemm(desc: Desc, A, B, bias, C, M=None, N=None, K=None, stream=None, knob
     of the descriptor's output type, all contiguous on the GPU (or raw device
     addresses with M, N, K given).  Inconsistent tensors raise ValueError
     before the library is called."""
-    import torch
-    if isinstance(A, torch.Tensor):
+    if _is_tensor(A):
         M, N, K = _check_gemm(desc, A, B, bias, C)
     if knobs is not None:
         kp = _knobs(knobs)
@@ -351,26 +408,45 @@ def dg_pack_b(B, out=None, stream=None) -> PackedB:
     return PackedB(out, K, N, torch.uint8 if b8 else B.dtype)
 
 
+def _check_packed(desc, A, Bp, bias, C):
+    """As _check_gemm for a packed B."""
+    want_a, want_b, want_c, need_bias = _types(desc)
+    if isinstance(Bp, PackedB):
+        sa, sc, N, data = A.shape, C.shape, Bp.N, Bp.data
+        if (len(sa) == 2 and len(sc) == 2 and sa[1] == Bp.K and sc[0] == sa[0] and sc[1] == N
+                and A.dtype in want_a and Bp.dtype in want_b and C.dtype is want_c
+                and A.is_contiguous() and C.is_contiguous() and A.is_cuda and C.is_cuda and data.is_cuda
+                and (not need_bias if bias is None else
+                     bias.dtype is _bf16 and bias.numel() == N and bias.is_contiguous() and bias.is_cuda)):
+            return sa[0], N, sa[1]
+    return _check_packed_named(desc, A, Bp, bias, C)
+
+
+def _check_packed_named(desc, A, Bp, bias, C):
+    import torch
+    _need(isinstance(Bp, PackedB), "Bp must come from dg_pack_b")
+    want_a, want_b = _in_dtypes(desc)
+    _need(A.dtype in want_a and Bp.dtype in want_b, "A must be %s and B %s" % (want_a[0], want_b[0]))
+    _need(A.dim() == 2 and C.dim() == 2 and A.is_contiguous() and C.is_contiguous(), "A and C must be row-major")
+    M, K = A.shape
+    N = Bp.N
+    _need(Bp.K == K, "inner dimensions differ (%d, %d)" % (K, Bp.K))
+    _need(tuple(C.shape) == (M, N), "C must be %d x %d" % (M, N))
+    _need(C.dtype == _out_dtype(desc), "C dtype must match the descriptor's output type")
+    if desc.fields["epilogue"] != "none":
+        _need(bias is not None, "the descriptor's epilogue needs a bias")
+    if bias is not None:
+        _need(bias.dtype == torch.bfloat16 and bias.numel() == N and bias.is_contiguous(),
+              "bias must be %d contiguous bf16 values" % N)
+    _on_device(A, C, bias, Bp.data)
+    return M, N, K
+
+
 def dg_gemm_packed(desc: Desc, A, Bp, bias, C, M=None, N=None, K=None, stream=None, knobs=None):
     """dg_gemm with B packed by dg_pack_b (the same bits); Bp a PackedB, or a
     raw device address with M, N, K given."""
-    import torch
-    if isinstance(A, torch.Tensor):
-        _need(isinstance(Bp, PackedB), "Bp must come from dg_pack_b")
-        want_a, want_b = _in_dtypes(desc)
-        _need(A.dtype in want_a and Bp.dtype in want_b, "A must be %s and B %s" % (want_a[0], want_b[0]))
-        _need(A.dim() == 2 and C.dim() == 2 and A.is_contiguous() and C.is_contiguous(), "A and C must be row-major")
-        M, K = A.shape
-        N = Bp.N
-        _need(Bp.K == K, "inner dimensions differ (%d, %d)" % (K, Bp.K))
-        _need(tuple(C.shape) == (M, N), "C must be %d x %d" % (M, N))
-        _need(C.dtype == _out_dtype(desc), "C dtype must match the descriptor's output type")
-        if desc.fields["epilogue"] != "none":
-            _need(bias is not None, "the descriptor's epilogue needs a bias")
-        if bias is not None:
-            _need(bias.dtype == torch.bfloat16 and bias.numel() == N and bias.is_contiguous(),
-                  "bias must be %d contiguous bf16 values" % N)
-        _on_device(A, C, bias, Bp.data)
+    if _is_tensor(A):
+        M, N, K = _check_packed(desc, A, Bp, bias, C)
         bptr = _ptr(Bp.data)
     else:
         bptr = _ptr(Bp)
@@ -389,8 +465,7 @@ def dg_gemm_noalloc(desc: Desc, A, B, bias, C, M=None, N=None, K=None, stream=No
     """dg_gemm through the entry point that allocates nothing: split-K
     partials go to the library's fixed per-device scratch (at most
     NOALLOC_SCRATCH_BYTES); calls that overlap on one device race."""
-    import torch
-    if isinstance(A, torch.Tensor):
+    if _is_tensor(A):
         M, N, K = _check_gemm(desc, A, B, bias, C)
     st = lib().dg_gemm_noalloc(desc.handle, _ptr(A), _ptr(B), _ptr(bias), _ptr(C), M, N, K, _stream(stream))
     if st != DG_OK:
@@ -400,9 +475,8 @@ def dg_gemm_noalloc(desc: Desc, A, B, bias, C, M=None, N=None, K=None, stream=No
 
 def dg_rowsum(desc: Desc, X, out, rows=None, cols=None, stream=None):
     """out[r] = balanced-tree reduction of row r of X (fp32, row-major)."""
-    import torch
-    if isinstance(X, torch.Tensor):
-        _need(X.dtype == torch.float32 and out.dtype == torch.float32 and X.dim() == 2, "X and out must be fp32")
+    if _is_tensor(X):
+        _need(X.dtype == _f32 and out.dtype == _f32 and X.dim() == 2, "X and out must be fp32")
         rows, cols = X.shape
         _need(out.numel() == rows, "out must hold one value per row")
         _need(X.is_contiguous() and out.is_contiguous(), "X and out must be contiguous")
@@ -416,8 +490,7 @@ def dg_rowsum(desc: Desc, X, out, rows=None, cols=None, stream=None):
 def dg_rmsnorm(desc: Desc, X, w, eps, Y, rows=None, cols=None, stream=None):
     """Y = RMS normalisation of the rows of X (fp32) scaled by w (bf16 or
     None), in the descriptor's order (its reduce must be "sumsq")."""
-    import torch
-    if isinstance(X, torch.Tensor):
+    if _is_tensor(X):
         rows, cols = _check_rows(desc, X, Y, w)
     st = lib().dg_rmsnorm(desc.handle, _ptr(X), _ptr(w), ctypes.c_float(eps), _ptr(Y), rows, cols, _stream(stream))
     if st != DG_OK:
@@ -427,10 +500,9 @@ def dg_rmsnorm(desc: Desc, X, w, eps, Y, rows=None, cols=None, stream=None):
 
 def dg_gemm_colsum(desc: Desc, A, B, bias, C, colsum, M=None, N=None, K=None, stream=None):
     """dg_gemm, then colsum[j] = the balanced tree down column j of C (fp32)."""
-    import torch
-    if isinstance(A, torch.Tensor):
+    if _is_tensor(A):
         M, N, K = _check_gemm(desc, A, B, bias, C)
-        _need(colsum.dtype == torch.float32 and colsum.numel() == N and colsum.is_contiguous(),
+        _need(colsum.dtype == _f32 and colsum.numel() == N and colsum.is_contiguous(),
               "colsum must be %d contiguous fp32 values" % N)
         _on_device(colsum)
     st = lib().dg_gemm_colsum(desc.handle, _ptr(A), _ptr(B), _ptr(bias), _ptr(C), _ptr(colsum), M, N, K,
@@ -443,8 +515,7 @@ def dg_gemm_colsum(desc: Desc, A, B, bias, C, colsum, M=None, N=None, K=None, st
 def dg_layernorm(desc: Desc, X, w, b, eps, Y, rows=None, cols=None, stream=None):
     """Y = layer normalisation of the rows of X (fp32), both row sums in the
     descriptor's order, then the bf16 weight and bias (each may be None)."""
-    import torch
-    if isinstance(X, torch.Tensor):
+    if _is_tensor(X):
         rows, cols = _check_rows(desc, X, Y, w, b)
     st = lib().dg_layernorm(desc.handle, _ptr(X), _ptr(w), _ptr(b), ctypes.c_float(eps), _ptr(Y), rows, cols,
                             _stream(stream))
@@ -456,8 +527,7 @@ def dg_layernorm(desc: Desc, X, w, b, eps, Y, rows=None, cols=None, stream=None)
 def dg_softmax(desc: Desc, X, Y, rows=None, cols=None, stream=None):
     """Y = softmax of the rows of X (fp32), the row sum in the descriptor's
     order (its reduce must be "sum")."""
-    import torch
-    if isinstance(X, torch.Tensor):
+    if _is_tensor(X):
         rows, cols = _check_rows(desc, X, Y)
     st = lib().dg_softmax(desc.handle, _ptr(X), _ptr(Y), rows, cols, _stream(stream))
     if st != DG_OK:
@@ -483,6 +553,7 @@ class AttnDesc:
         f = dict(self.DEFAULTS)
         f.update({k: v for k, v in fields.items() if k != "model"})
         self.fields = f
+        self.types = None
         p = dg_attn_params()
         p.struct_size = ctypes.sizeof(dg_attn_params)
         p.key_block = int(f["key_block"])
@@ -507,22 +578,40 @@ class AttnDesc:
             self.handle = None
 
 
+def _check_attention(desc, Q, K, V, O):
+    """Shapes, dtypes and layout of an attention call; returns (H, Lq, Lk, dim)."""
+    sq, sk = Q.shape, K.shape
+    if desc.types is None:
+        desc.types = _out_dtype(desc)
+    if (len(sq) == 3 and len(sk) == 3 and sk[0] == sq[0] and sk[2] == sq[2] and V.shape == sk and O.shape == sq
+            and Q.dtype is _bf16 and K.dtype is _bf16 and V.dtype is _bf16 and O.dtype is desc.types
+            and Q.is_contiguous() and K.is_contiguous() and V.is_contiguous() and O.is_contiguous()
+            and Q.is_cuda and K.is_cuda and V.is_cuda and O.is_cuda):
+        return sq[0], sq[1], sk[1], sq[2]
+    return _check_attention_named(desc, Q, K, V, O)
+
+
+def _check_attention_named(desc, Q, K, V, O):
+    import torch
+    _need(Q.dtype == torch.bfloat16 and K.dtype == torch.bfloat16 and V.dtype == torch.bfloat16,
+          "Q, K and V must be bf16")
+    _need(Q.dim() == 3 and K.dim() == 3 and V.dim() == 3 and O.dim() == 3, "Q, K, V and O are (H, L, d)")
+    H, Lq, dim = Q.shape
+    Lk = K.shape[1]
+    _need(tuple(K.shape) == (H, Lk, dim) and tuple(V.shape) == (H, Lk, dim), "K and V must be (H, Lk, d)")
+    _need(tuple(O.shape) == (H, Lq, dim), "O must be (H, Lq, d)")
+    _need(O.dtype == _out_dtype(desc), "O dtype must match the descriptor's output type")
+    _need(all(t.is_contiguous() for t in (Q, K, V, O)), "Q, K, V and O must be contiguous")
+    _on_device(Q, K, V, O)
+    return H, Lq, Lk, dim
+
+
 def dg_attention(desc: AttnDesc, Q, K, V, O, qk_scale, H=None, Lq=None, Lk=None, dim=None, stream=None):
     """O = attention in the descriptor's order: Q (H, Lq, d), K and V (H, Lk,
     d) bf16, O (H, Lq, d) of the descriptor's output type, contiguous on the
     GPU (or raw device addresses with the sizes given)."""
-    import torch
-    if isinstance(Q, torch.Tensor):
-        _need(Q.dtype == torch.bfloat16 and K.dtype == torch.bfloat16 and V.dtype == torch.bfloat16,
-              "Q, K and V must be bf16")
-        _need(Q.dim() == 3 and K.dim() == 3 and V.dim() == 3 and O.dim() == 3, "Q, K, V and O are (H, L, d)")
-        H, Lq, dim = Q.shape
-        Lk = K.shape[1]
-        _need(tuple(K.shape) == (H, Lk, dim) and tuple(V.shape) == (H, Lk, dim), "K and V must be (H, Lk, d)")
-        _need(tuple(O.shape) == (H, Lq, dim), "O must be (H, Lq, d)")
-        _need(O.dtype == _out_dtype(desc), "O dtype must match the descriptor's output type")
-        _need(all(t.is_contiguous() for t in (Q, K, V, O)), "Q, K, V and O must be contiguous")
-        _on_device(Q, K, V, O)
+    if _is_tensor(Q):
+        H, Lq, Lk, dim = _check_attention(desc, Q, K, V, O)
     st = lib().dg_attention(desc.handle, _ptr(Q), _ptr(K), _ptr(V), _ptr(O), H, Lq, Lk, dim,
                             ctypes.c_float(qk_scale), _stream(stream))
     if st != DG_OK:
