@@ -156,6 +156,7 @@ bool capturing(hipStream_t st) {
 struct AutoConfig {
   int kern, tm, tn, order, occ, depth, slab_k;
 };
+constexpr int RING = 100;   // dg_gemm_ring.hip: no knob
 
 // The ping-pong kernels address their operands with 31-bit byte offsets from
 // the block's first A row and the part's first B row.
@@ -202,19 +203,31 @@ int64_t mixed_split(int64_t M, int64_t N, int S, int ncu) {
   return split;
 }
 
-AutoConfig auto_config(int64_t M, int64_t N, int S) {
-  if (M <= 32) {
-    if (S * ((N + 63) / 64) >= 256) return {4, 16, 64, 0, 0, 4, 64};
-    return {4, 16, M <= 16 ? 16 : 32, 0, 0, 2, 256};
+// The kernel of a product on a chunk grid.  fits: pp_fits, the offsets of the
+// kernels that load through buffer resources.
+AutoConfig auto_config(int64_t M, int64_t N, int S, int ncu, bool fits) {
+  auto tiles = [&](int64_t tm, int64_t tn) { return S * ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
+  // few rows: 16-column blocks while they are one round of the chip (1 x 4096
+  // x 4096 11.9 us; 64-column ring blocks 14.6), past it the ring (1 x 5120 x
+  // 4096 14.9 against 18.4, 1 x 14272 x 3328 15.9 against 54)
+  if (M <= 32 && 4 * S * ((N + 63) / 64) <= ncu) return {4, 16, M <= 16 ? 16 : 32, 0, 0, 2, 256};
+  if (!fits) {
+    if (M <= 32) return {4, 16, 64, 0, 0, 4, 64};
+    if (M <= 128) return {4, 32, 64, 0, 0, 2, 256};
+    return {3, 64, 128, 3, 2, 0, 0};
   }
-  if (M <= 128) return {4, 32, 64, 0, 0, 2, 256};
-  const int64_t tiles256 = S * ((M + 255) / 256) * ((N + 255) / 256);
-  const int64_t tiles128 = S * ((M + 127) / 128) * ((N + 127) / 128);
   // 256 x 256 blocks, each XCD given a contiguous range of them (2-3 % over
-  // row-major order at 4096 x 4096 x 4096 on MI355X)
-  if (tiles256 >= 192) return {5, 256, 256, 3, 0, 0, 0};
-  if (tiles128 >= 128) return {5, 128, 128, 3, 0, 0, 0};
-  return {3, 64, 128, 3, 2, 0, 0};
+  // row-major order at 4096 x 4096 x 4096 on MI355X), where they fill three
+  // quarters of the chip: 4096 x 4096 x 4096 117 us (the ring 132); below,
+  // 2560 x 4096 x 4096 (160 blocks) 112 (the ring 90)
+  if (tiles(256, 256) >= 192) return {5, 256, 256, 3, 0, 0, 0};
+  // the ring's blocks by rounds of the chip; a round of 4096 k took 36 us
+  // with 128 x 128 blocks, 25 with 64 x 128, 17.5 with 64 x 64
+  auto cost = [&](int64_t t, double round) { return (double)((t + ncu - 1) / ncu) * round; };
+  const double c128 = cost(tiles(128, 128), 36), c64w = cost(tiles(64, 128), 25), c64 = cost(tiles(64, 64), 17.5);
+  if (c64 <= c64w && c64 <= c128) return {RING, 64, 64, 3, 0, 0, 0};
+  if (c64w <= c128) return {RING, 64, 128, 3, 0, 0, 0};
+  return {RING, 128, 128, 3, 0, 0, 0};
 }
 
 }  // namespace
@@ -533,9 +546,8 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
   }
   if (kern == 1 && (tm || tn)) return DG_ERR_UNSUPPORTED;
   if (kern == 0 && tiled_ok) {
-    AutoConfig c = auto_config(M, N, a.S);
-    if (c.kern == 5 && !pp_fits(a)) c = {3, 64, 128, 3, 2, 0, 0};
-    if (c.kern == 5 && c.tm == 256 && c.tn == 256) {
+    AutoConfig c = auto_config(M, N, a.S, cu_count(), pp_fits(a));
+    if (c.kern == 5) {
       const int64_t sp = mixed_split(M, N, a.S, cu_count());
       if (sp >= 0) {
         // the width mix keeps row-major block order (measured best for it)
@@ -571,8 +583,7 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
       if (((M + 127) / 128) * ((N + 63) / 64) > INT32_MAX) odd = false;
       if (odd) kern = 12;
     } else if (odd) {
-      AutoConfig c = auto_config(M, N, a.S);
-      if (c.kern == 5 && !pp_fits(a)) c = {3, 64, 128, 3, 2, 0, 0};
+      const AutoConfig c = auto_config(M, N, a.S, cu_count(), pp_fits(a));
       kern = c.kern;
       tm = c.tm;
       tn = c.tn;
@@ -585,7 +596,10 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
     *fused = true;
   }
   hipError_t e;
-  if (odd) {
+  if (kern == RING) {
+    a.order = order;
+    e = dg::launch_gemm_ring(a, tm, tn, odd, st);
+  } else if (odd) {
     a.order = kern == 12 ? 1 : order;
     e = kern == 12 ? dg::launch_gemm_odd_tc(a, tc_levels, st) : dg::launch_gemm_odd(a, kern, tm, tn, st);
   } else if (kern == 11) {

@@ -4,9 +4,10 @@
 // kernels (dg_gemm_tile.h, whose UN comment says how chunks are loaded where
 // they lie and what the last slab mends); these used to run on gemm_generic,
 // one wave per 16 x 16 outputs with element loads and no reuse.  Measured
-// on MI355X before and after: 515 x 3001 x 2047 510 -> 31.5 us, 2047 x 14335 x
-// 4095 16.7 ms -> 305 us (the aligned 2048 x 14336 x 4096: 223), 1 x 4095 x
-// 4095 137 -> 13.5, tile tree 1000 x 3001 x 1001 481 -> 63.
+// on MI355X before and after: 2047 x 14335 x 4095 16.7 ms -> 305 us (the
+// aligned 2048 x 14336 x 4096: 223), 1 x 4095 x 4095 137 -> 13.5, tile tree
+// 1000 x 3001 x 1001 481 -> 63.  The sizes between the few-row kernels and the
+// 256-row blocks run on dg_gemm_ring.hip.
 #include "dg_gemm_tile.h"
 
 namespace dg {

@@ -122,6 +122,10 @@ hipError_t launch_gemm_f8(const GemmArgs& a, int tile, hipStream_t s);
 // loaded direct to LDS (the tiled layout's conditions; M K and K N below
 // 2^30 elements)
 hipError_t launch_gemm_b16n(const GemmArgs& a, hipStream_t s);
+// blocks of 128 x 128, 64 x 128 or 64 x 64 on a direct-to-LDS ring (buffer offsets below
+// 2^31; the tiled layout's conditions, or odd: any size and alignment with N, K >= 8,
+// contiguous parts)
+hipError_t launch_gemm_ring(const GemmArgs& a, int tile_m, int tile_n, bool odd, hipStream_t s);
 // the few-row (4), v3 (3) and ping-pong (5) kernels, and the tile-combine one, on
 // operands of any size and alignment (N, K >= 8; contiguous parts)
 hipError_t launch_gemm_odd(const GemmArgs& a, int kern, int tile_m, int tile_n, hipStream_t s);

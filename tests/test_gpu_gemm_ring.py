@@ -1,0 +1,77 @@
+"""GPU parity of the ring GEMM kernels at the edges of their blocks, slots and
+parts: every block shape, K from one chunk to one slab more than the slots
+hold and around it, parts shorter than a slab, aligned and odd, against the
+generic kernel on every output and the CPU oracle on some rows, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2609_11356_amd import inputs
+from tests.gpu_util import assert_bits_equal, host_bits
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dg():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_11356_amd import dg as _dg
+    _dg.lib()
+    return _dg
+
+
+def device(bits, dtype, off):
+    """A matrix of 16-bit patterns `off` elements into a buffer of NaN patterns."""
+    import torch
+    buf = torch.full((bits.size + off + 8,), -1, dtype=torch.int16, device="cuda")
+    buf[off:off + bits.size] = torch.from_numpy(bits.reshape(-1).view(np.int16)).cuda()
+    return buf[off:off + bits.size].view(dtype).view(bits.shape)
+
+
+# 64 x 64 blocks, few rows over many columns, 64 x 128, 128 x 128 (a block,
+# its edge, one row or chunk past it)
+SIZES = [(33, 104), (64, 64), (65, 200), (128, 72), (3, 6408), (32, 5000), (1000, 1104), (961, 2056), (2000, 2056)]
+DESCS = [dict(), dict(out="bf16", epilogue="bias_silu", epi_round="pre_act"), dict(in_dtype="f16", out="bf16", epilogue="bias"),
+         dict(split_k=3, split_combine="tree", partial="bf16", out="bf16", epilogue="bias"), dict(split_k=2, in_dtype="f16"),
+         dict(tail="first", tile_k=64)]
+KS = [8, 64, 72, 128, 192, 256, 320, 328, 384, 448, 520]
+
+
+@pytest.mark.parametrize("odd", [0, 1])
+@pytest.mark.parametrize("size", SIZES)
+@pytest.mark.parametrize("di", range(len(DESCS)))
+def test_ring(dg, di, size, odd):
+    import torch
+    desc = dict(tile_k=32)
+    desc.update(DESCS[di])
+    f16 = desc.get("in_dtype") == "f16"
+    dt = torch.float16 if f16 else torch.bfloat16
+    spread = inputs.spread_f16 if f16 else inputs.spread_bf16
+    for K in KS if size[0] < 900 else KS[di % 3::3]:
+        M, N = size[0], size[1] - 3 * odd
+        if desc.get("tail") != "first":
+            K = K + 1 if odd else K
+        parts = desc.get("split_k", 1)
+        if parts > 1 and (parts - 1) * (-(-K // (32 * parts)) * 32) >= K:
+            continue                              # the cut plan would leave a part empty
+        A, B = spread(di + 17 * M + K, (M, K)), spread(di + 17 * M + 1, (K, N))
+        bias = inputs.normal_bf16(M + 2, (N,), 1.0) if "epilogue" in desc else None
+        A[M // 2, 0] = 0x7FFF                     # a NaN row, an infinite one and a NaN column
+        A[M // 3, K // 2] = 0x7C00 if f16 else 0x7F80
+        B[K // 2, 5] = 0x7FFF
+        print("size %s K %d odd %d desc %s" % ((M, N), K, odd, desc), flush=True)
+        dA, dB = device(A, dt, odd), device(B, dt, odd)
+        db = None if bias is None else device(bias, torch.bfloat16, odd)
+        ct = torch.bfloat16 if desc.get("out") == "bf16" else torch.float32
+        buf = torch.full((M * N + 16,), 7.0, dtype=ct, device="cuda")
+        C, ref = buf[8 + odd:8 + odd + M * N].view(M, N), torch.empty((M, N), dtype=ct, device="cuda")
+        d = dg.Desc(**desc)
+        dg.dg_gemm(d, dA, dB, db, C)
+        dg.dg_gemm(d, dA, dB, db, ref, knobs=dict(kernel=1))
+        torch.cuda.synchronize()
+        assert_bits_equal(host_bits(C), host_bits(ref), "M %d N %d K %d %s" % (M, N, K, desc))
+        rows = np.unique([0, M // 3, M // 2, M - 1])
+        assert_bits_equal(host_bits(C)[rows], oracle.gemm(desc, A[rows], B, bias), "M %d N %d K %d %s" % (M, N, K, desc))
+        assert (buf[:8 + odd] == 7).all() and (buf[8 + odd + M * N:] == 7).all()   # nothing written outside
