@@ -321,13 +321,14 @@ typedef struct {
                       0, 16, 32 or 64 rows per wave, depth its ring of k
                       blocks), 12 the tile-combine kernel: tile_combine
                       DG_SEQ or DG_TREE, or fma = 0, on 128 x 64 blocks of
-                      four waves (no other knob; the library's choice for
-                      those descriptors when K and N are multiples of 8, the
+                      four waves (no other knob; K and N multiples of 8, the
                       operands 16-byte aligned, every part's tile boundaries
                       on 32-k steps from its start, fma = 0 only with the
-                      16x16x32 instruction, a tree part at most 128 tiles;
-                      otherwise DG_ERR_UNSUPPORTED, and kernel 0 runs the
-                      generic kernel 1).  Binary16 operands
+                      16x16x32 instruction, a tree part at most 128 tiles,
+                      otherwise DG_ERR_UNSUPPORTED; the library's choice
+                      there for fma = 0, while for fma = 1 kernel 0 runs
+                      smaller blocks that have no knob, on any size of at
+                      least 8 and any alignment and up to 256 tiles).  Binary16 operands
                       (in_dtype = DG_IN_F16) run on kernels 0, 1, 3, 4, 5, 6,
                       9 and 12; kernels 2, 7, 8 and 10 return DG_ERR_UNSUPPORTED.
                       An e4m3 B (DG_IN_BF16_E4M3) runs on kernel 1 (row-major)

@@ -156,7 +156,7 @@ bool capturing(hipStream_t st) {
 struct AutoConfig {
   int kern, tm, tn, order, occ, depth, slab_k;
 };
-constexpr int RING = 100;   // dg_gemm_ring.hip: no knob
+constexpr int RING = 100, RING_TILES = 101;   // the ring kernels: no knobs
 
 // The ping-pong kernels address their operands with 31-bit byte offsets from
 // the block's first A row and the part's first B row.
@@ -203,6 +203,21 @@ int64_t mixed_split(int64_t M, int64_t N, int S, int ncu) {
   return split;
 }
 
+// The ring kernels' blocks, by rounds of the chip.  A round of 4096 k took
+// 36 us with 128 x 128 blocks, 25 with 64 x 128, 17.5 with one 64 x 64 block
+// per CU and 28 with two; with tiles closed every 64 k (a 128 x 128 block
+// holds at most a three-level tree: big) 43, 30, 26 and 31.
+void ring_config(int64_t M, int64_t N, int S, int ncu, bool tiles, bool big, int* tm, int* tn) {
+  auto rounds = [&](int64_t bm, int64_t bn, int64_t per) {
+    return (double)((S * ((M + bm - 1) / bm) * ((N + bn - 1) / bn) + per - 1) / per);
+  };
+  const double c128 = rounds(128, 128, ncu) * (tiles ? 43 : 36), c64w = rounds(64, 128, ncu) * (tiles ? 30 : 25);
+  const double c64 = rounds(64, 64, ncu) == 1 ? (tiles ? 26 : 17.5) : rounds(64, 64, 2 * ncu) * (tiles ? 31 : 28);
+  const bool b128 = big && c128 < c64w && c128 < c64;
+  *tm = b128 ? 128 : 64;
+  *tn = b128 || c64w < c64 ? 128 : 64;
+}
+
 // The kernel of a product on a chunk grid.  fits: pp_fits, the offsets of the
 // kernels that load through buffer resources.
 AutoConfig auto_config(int64_t M, int64_t N, int S, int ncu, bool fits) {
@@ -221,13 +236,9 @@ AutoConfig auto_config(int64_t M, int64_t N, int S, int ncu, bool fits) {
   // quarters of the chip: 4096 x 4096 x 4096 117 us (the ring 132); below,
   // 2560 x 4096 x 4096 (160 blocks) 112 (the ring 90)
   if (tiles(256, 256) >= 192) return {5, 256, 256, 3, 0, 0, 0};
-  // the ring's blocks by rounds of the chip; a round of 4096 k took 36 us
-  // with 128 x 128 blocks, 25 with 64 x 128, 17.5 with 64 x 64
-  auto cost = [&](int64_t t, double round) { return (double)((t + ncu - 1) / ncu) * round; };
-  const double c128 = cost(tiles(128, 128), 36), c64w = cost(tiles(64, 128), 25), c64 = cost(tiles(64, 64), 17.5);
-  if (c64 <= c64w && c64 <= c128) return {RING, 64, 64, 3, 0, 0, 0};
-  if (c64w <= c128) return {RING, 64, 128, 3, 0, 0, 0};
-  return {RING, 128, 128, 3, 0, 0, 0};
+  AutoConfig c = {RING, 0, 0, 3, 0, 0, 0};
+  ring_config(M, N, S, ncu, false, true, &c.tm, &c.tn);
+  return c;
 }
 
 }  // namespace
@@ -522,14 +533,20 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
   }
   int tc_levels = 2;
   while (tc_levels < 7 && part_tiles > ((int64_t)1 << tc_levels)) ++tc_levels;
+  // the ring's tree (fma = 1): at most 256 tiles per part
+  const bool ring_tiles = tc_ok && p.fma == 1 && (p.tile_combine != DG_TREE || part_tiles <= 256) && pp_fits(a);
   if (p.tile_combine == DG_TREE && part_tiles > 128) tc_ok = false;
   if (scalar) {
     tiled_ok = false;
     kern = 9;
   }
   if (kern == 12 && !tc_ok) return DG_ERR_UNSUPPORTED;
+  if (kern == 0 && !tiled_ok && ring_tiles) {
+    kern = RING_TILES;
+    ring_config(M, N, a.S, cu_count(), true, p.tile_combine == DG_SEQ || part_tiles <= 8, &tm, &tn);
+  }
   if (kern == 0 && !tiled_ok && tc_ok) kern = 12;
-  if (kern >= 2 && kern != 9 && kern != 11 && kern != 12 && kern != 13 && !tiled_ok) return DG_ERR_UNSUPPORTED;
+  if (kern >= 2 && kern != 9 && kern != 11 && kern != 12 && kern != 13 && kern < RING && !tiled_ok) return DG_ERR_UNSUPPORTED;
   if (kern == 14 && !(M * K < 0x3fffffff && K * N < 0x3fffffff)) return DG_ERR_UNSUPPORTED;
   if (strided && kern == 0) {
     const int tmc = M <= 16 ? 16 : M <= 32 ? 32 : 64;
@@ -579,9 +596,11 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
     }
     if (gen) {
       if (d->group != 32 && p.fma == 0) odd = false;
-      if (p.tile_k % 32 || (p.tile_combine == DG_TREE && (p.fma == 0 || part_tiles > 128))) odd = false;
+      if (p.tile_k % 32 || (p.tile_combine == DG_TREE && (p.fma == 0 || part_tiles > 256))) odd = false;
+      if (p.fma == 1 && !pp_fits(a)) odd = false;
       if (((M + 127) / 128) * ((N + 63) / 64) > INT32_MAX) odd = false;
-      if (odd) kern = 12;
+      if (odd) kern = p.fma == 1 ? RING_TILES : 12;
+      if (kern == RING_TILES) ring_config(M, N, a.S, cu_count(), true, p.tile_combine == DG_SEQ || part_tiles <= 8, &tm, &tn);
     } else if (odd) {
       const AutoConfig c = auto_config(M, N, a.S, cu_count(), pp_fits(a));
       kern = c.kern;
@@ -599,9 +618,12 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
   if (kern == RING) {
     a.order = order;
     e = dg::launch_gemm_ring(a, tm, tn, odd, st);
+  } else if (kern == RING_TILES) {
+    a.order = 3;
+    e = dg::launch_gemm_ring_tiles(a, (int)part_tiles, tm, tn, odd, st);
   } else if (odd) {
     a.order = kern == 12 ? 1 : order;
-    e = kern == 12 ? dg::launch_gemm_odd_tc(a, tc_levels, st) : dg::launch_gemm_odd(a, kern, tm, tn, st);
+    e = kern == 12 ? dg::launch_gemm_odd_tc(a, st) : dg::launch_gemm_odd(a, kern, tm, tn, st);
   } else if (kern == 11) {
     e = dg::launch_gemm_panel(a, panel_tms, panel_depth, panel_avec, st);
   } else if (kern == 14) {

@@ -5,9 +5,9 @@
 // they lie and what the last slab mends); these used to run on gemm_generic,
 // one wave per 16 x 16 outputs with element loads and no reuse.  Measured
 // on MI355X before and after: 2047 x 14335 x 4095 16.7 ms -> 305 us (the
-// aligned 2048 x 14336 x 4096: 223), 1 x 4095 x 4095 137 -> 13.5, tile tree
-// 1000 x 3001 x 1001 481 -> 63.  The sizes between the few-row kernels and the
-// 256-row blocks run on dg_gemm_ring.hip.
+// aligned 2048 x 14336 x 4096: 223), 1 x 4095 x 4095 137 -> 13.5.  The sizes between the
+// few-row kernels and the 256-row blocks run on the ring (dg_gemm_ring.h), as do
+// tile chains and trees with fma = 1.
 #include "dg_gemm_tile.h"
 
 namespace dg {
@@ -25,14 +25,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   v3_body<BM, BN, WM, WN, BK, F16, DG_CARRY, false, 1, true>(a, (int64_t)ty * BM, (int64_t)tx * BN);
 }
 
-template <int COMB, bool FMA0, int L, bool F16>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COMB == DG_TREE && L >= 5 ? 1 : 2,
-                                                                     COMB == DG_TREE && L >= 5 ? 1 : 2))) void
-odd_tc(GemmArgs a) {
+template <int COMB, bool F16>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void odd_fma0(GemmArgs a) {
   const int tiles_m = (int)((a.M + 127) / 128);
   int ty, tx;
   grouped_tile(blockIdx.x, tiles_m, gridDim.x / tiles_m, a.order, &ty, &tx);
-  v3_body<128, 64, 2, 2, 32, F16, COMB, FMA0, L, true>(a, (int64_t)ty * 128, (int64_t)tx * 64);
+  v3_body<128, 64, 2, 2, 32, F16, COMB, true, 1, true>(a, (int64_t)ty * 128, (int64_t)tx * 64);
 }
 
 template <int BM, int BN, int BK, bool F16>
@@ -72,12 +70,12 @@ static hipError_t launch_pp_o(const GemmArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int COMB, bool FMA0, int L>
-static hipError_t launch_tc_o(const GemmArgs& a, hipStream_t st) {
+template <int COMB>
+static hipError_t launch_fma0_o(const GemmArgs& a, hipStream_t st) {
   const int64_t tm = (a.M + 127) / 128, tn = (a.N + 63) / 64;
   dim3 grid((unsigned)(tm * tn), 1, (unsigned)a.S);
-  if (a.in_f16) hipLaunchKernelGGL((odd_tc<COMB, FMA0, L, true>), grid, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((odd_tc<COMB, FMA0, L, false>), grid, dim3(256), 0, st, a);
+  if (a.in_f16) hipLaunchKernelGGL((odd_fma0<COMB, true>), grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((odd_fma0<COMB, false>), grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
@@ -93,19 +91,10 @@ hipError_t launch_gemm_odd(const GemmArgs& a, int kern, int tm, int tn, hipStrea
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_gemm_odd_tc(const GemmArgs& a, int levels, hipStream_t st) {
-  const bool fma0 = a.fma == 0;
-  if (a.tile_combine == DG_CARRY) return fma0 ? launch_tc_o<DG_CARRY, true, 1>(a, st) : hipErrorInvalidValue;
-  if (a.tile_combine == DG_SEQ) return fma0 ? launch_tc_o<DG_SEQ, true, 1>(a, st) : launch_tc_o<DG_SEQ, false, 1>(a, st);
-  if (a.tile_combine != DG_TREE || fma0) return hipErrorInvalidValue;
-  switch (levels) {
-    // four levels do not fit two workgroups per CU beside the unaligned loads' addresses
-    case 2: case 3: return launch_tc_o<DG_TREE, false, 3>(a, st);
-    case 4: case 5: return launch_tc_o<DG_TREE, false, 5>(a, st);
-    case 6: return launch_tc_o<DG_TREE, false, 6>(a, st);
-    case 7: return launch_tc_o<DG_TREE, false, 7>(a, st);
-    default: return hipErrorInvalidValue;
-  }
+hipError_t launch_gemm_odd_tc(const GemmArgs& a, hipStream_t st) {
+  if (a.fma != 0) return hipErrorInvalidValue;
+  if (a.tile_combine == DG_CARRY) return launch_fma0_o<DG_CARRY>(a, st);
+  return a.tile_combine == DG_SEQ ? launch_fma0_o<DG_SEQ>(a, st) : hipErrorInvalidValue;
 }
 
 }  // namespace dg

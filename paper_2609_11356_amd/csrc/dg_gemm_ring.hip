@@ -1,283 +1,7 @@
-// dg_gemm_ring.hip -- bf16 / binary16 GEMM on BM x BN blocks with a ring of
-// NS LDS slots filled by direct-to-LDS loads, for the sizes between the
-// few-row kernels and the 256-row blocks: the order and bits of the other
-// chunk-grid kernels (8-k chunks in increasing k through one accumulator, on
-// the 32x32x16 instruction).
-//
-// Bound: latency on short grids, LDS and the load path on full ones.  The v3
-// kernel (two slabs ahead through registers, LDS writes, a barrier between)
-// took 1150 cycles per 64-k slab of a 64 x 128 block however few MFMAs it
-// held; the ping-pong kernel 1400 per slab of 128 x 128 (512 of MFMA).  Here
-// a slab's loads have no register or LDS-write stage, two to five slabs are
-// in flight, and the wave reads the next 16-k step's fragments while it issues
-// the MFMAs of this one.  One barrier per slab, before its last step:
-//   wait until the wave's own loads of slab s + 1 have landed, barrier; then
-//   the fragments of slab s + 1 may be read (every wave's loads of it are
-//   in), and the slot of slab s - 1 may be filled again (every wave has
-//   issued its MFMAs of slab s - 1): its NI loads, for slab s + NS - 1, are
-//   spread over the next four steps.
-// Slabs past the part end are zeros (their chunks leave accumulators as they
-// are).  A [row][k], 128-byte rows, chunk c of row r at c ^ ((r / 2) mod 8):
-// 16 consecutive rows of one chunk on 16 slots of a 256-byte bank window.
-// B [k][n]: 64 bytes of 4 k rows per half wave of a transposing read, on 16
-// slots.
-// Measured on MI355X before and after (v3, ping-pong and few-row kernels):
-// 1024 x 4096 x 4096 44.5 -> 37.0 us, 512 x 4096 x 4096 39 -> 24.6, 256 x 4096
-// x 4096 38 -> 17.9, 1024 x 1024 x 1024 13.5 -> 7.3, 128 x 14336 x 4096 89 ->
-// 25.6, 32 x 14336 x 4096 36.8 -> 21.9, 1 x 14272 x 3328 54 -> 16; odd sizes
-// 515 x 3001 x 2047 33 -> 21.  Blocks of 128 x 128 with 2 x 4 waves beat 2 x 2
-// (37 against 42 us) and 4 x 2 (39); the 64 x 128 ones 2 x 2 (24.6 against
-// 26); 64 x 64 with six slots beats four (17.9 against 19.7), which leave a
-// CU two blocks (28 us for 512 of them, where 256 of 64 x 128 take 25).
-// UN (odd sizes): chunks are loaded where they lie, as in dg_gemm_tile.h, and
-// the lanes that loaded the last slab mend it in LDS before it is read.
-#include "dg_gemm_tile.h"
+// dg_gemm_ring.hip -- the ring GEMM (dg_gemm_ring.h) with a carried accumulator.
+#include "dg_gemm_ring.h"
 
 namespace dg {
-
-namespace {
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef __attribute__((address_space(3))) void* lds_void;
-
-// LDS array number ID of the workgroup (one per slot and operand, so that the
-// compiler can tell a read from the loads in flight).
-template <int ID, int BYTES>
-__device__ __forceinline__ uint16_t* ring_array() {
-  __shared__ __attribute__((aligned(1024))) uint16_t L[BYTES / 2];
-  return L;
-}
-
-__device__ __forceinline__ void ring_barrier() {
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-template <bool F16>
-__device__ __forceinline__ void mfma32(floatx16& c, const shortx8& a, const shortx8& b) {
-  if constexpr (F16)
-    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-  else
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
-}  // namespace
-
-template <int BM, int BN, int WM, int WN, int NS, bool F16, bool UN>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_ring(GemmArgs a) {
-  constexpr int NW = WM * WN, BK = 64, WTM = BM / WM, WTN = BN / WN, TM = WTM / 32, TN = WTN / 32;
-  constexpr int BROW = BN / 8, A_BYTES = BM * BK * 2, B_BYTES = BK * BN * 2;
-  constexpr int NIA = A_BYTES / 1024 / NW, NIB = B_BYTES / 1024 / NW, NI = NIA + NIB;   // loads per wave and slab
-  static_assert(A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0 && TM >= 1 && TN >= 1, "whole loads and tiles");
-  static_assert((BROW == 8 || BROW == 16 || BROW == 32) && NS >= 3 && (NS - 1) * NI <= 63, "the waits fit the load counter");
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
-  const int tiles_m = (int)((a.M + BM - 1) / BM);
-  int ty, tx;
-  grouped_tile(blockIdx.x, tiles_m, gridDim.x / tiles_m, a.order, &ty, &tx);
-  const int64_t i0 = (int64_t)ty * BM, j0 = (int64_t)tx * BN;
-  const int s = blockIdx.z;
-  const int64_t k0 = a.cuts[s], k1 = a.cuts[s + 1];
-  const int nslab = (int)((k1 - k0 + BK - 1) / BK);
-  auto swA = [](int r) { return (r >> 1) & 7; };
-  auto swB = [](int k) { return BROW >= 16 ? (k & 3) << 2 : ((k >> 1) & 1) << 2; };
-
-  // load t of the wave fills 1 KB: A rows 8 (NIA wave + t).., or B rows; each
-  // lane fetches the chunk that belongs at its place (a row past M or a
-  // column past N lies past the resource's end and reads zero)
-  constexpr uint32_t OOB = 0x80000000u;
-  constexpr int BRUN = 64 / BROW;               // B rows per load
-  // place of the lane's chunk of load t: A row and first k, B k row and first column
-  auto place_a = [&](int t, int* row, int* k) { *row = (NIA * wave + t) * 8 + lane / 8; *k = 8 * ((lane & 7) ^ swA(*row)); };
-  auto place_b = [&](int u, int* kr, int* col) {
-    *kr = (NIB * wave + u) * BRUN + lane / BROW;
-    *col = 8 * ((lane % BROW) ^ swB(*kr));
-  };
-  // UN: the resources start on 16 bytes, mis* bytes before the operands' own start
-  const uint16_t *pA = a.A + i0 * a.K, *pB = a.B + k0 * a.N;
-  const uint32_t misA = UN ? (uint32_t)((uintptr_t)pA & 15) : 0, misB = UN ? (uint32_t)((uintptr_t)pB & 15) : 0;
-  uint32_t off[NI];
-  int kl[NI];   // the chunk is loaded while this k lies before the part end
-#pragma unroll
-  for (int t = 0; t < NIA; ++t) {
-    int row, k;
-    place_a(t, &row, &k);
-    off[t] = i0 + row < a.M ? (uint32_t)((row * a.K + k) * 2) + misA : OOB;
-    kl[t] = UN && k1 == a.K && i0 + row == a.M - 1 ? k + 7 : k;             // the matrix's last chunk only whole
-  }
-#pragma unroll
-  for (int u = 0; u < NIB; ++u) {
-    int kr, col;
-    place_b(u, &kr, &col);
-    off[NIA + u] = j0 + col < a.N ? (uint32_t)((kr * a.N + j0 + col) * 2) + misB : OOB;
-    kl[NIA + u] = UN && k1 == a.K && j0 + col + 8 > a.N ? kr + 1 : kr;
-  }
-  const int64_t recA = (a.M - i0) * a.K * 2 + misA, recB = (a.K - k0) * a.N * 2 + misB;
-  const __amdgpu_buffer_rsrc_t rA = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)((const char*)pA - misA), (short)0, (int)(recA < 0x7fffffff ? recA : 0x7fffffff), 0x00020000);
-  const __amdgpu_buffer_rsrc_t rB = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)((const char*)pB - misB), (short)0, (int)(recB < 0x7fffffff ? recB : 0x7fffffff), 0x00020000);
-  const int stepB = (int)(BK * a.N * 2);
-  // load t of slab sl into slot X
-  auto dma = [&](int sl, auto X, auto T) {
-    constexpr int x = decltype(X)::value, t = decltype(T)::value;
-    const int left = sl < nslab ? (int)(k1 - k0) - sl * BK : 0;   // k of the part from the slab on
-    const uint32_t o = kl[t] < left ? off[t] : OOB;
-    if constexpr (t < NIA)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (lds_void)(ring_array<x, A_BYTES + B_BYTES>() + 512 * (NIA * wave + t)), 16, o,
-                                               sl < nslab ? (int)(k0 + sl * BK) * 2 : 0, 0, 0);
-    else
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rB, (lds_void)(ring_array<x, A_BYTES + B_BYTES>() + A_BYTES / 2 + 512 * (NIB * wave + t - NIA)), 16, o, sl < nslab ? sl * stepB : 0, 0, 0);
-  };
-
-  // UN: the part's last slab, in slot X, is mended by the lanes that loaded
-  // it: elements of A at or past the part end are cleared, and the chunk that
-  // ends each matrix is put together from single elements.
-  auto mend = [&](auto X) {
-    uint16_t* L = ring_array<decltype(X)::value, A_BYTES + B_BYTES>() + 8 * lane;
-    const int64_t kb = k0 + (int64_t)(nslab - 1) * BK;
-    static_for<0, NIA>([&](auto T) {
-      int row, k;
-      place_a(decltype(T)::value, &row, &k);
-      u32x4* p = (u32x4*)(L + 512 * (NIA * wave + decltype(T)::value));
-      if (i0 + row < a.M && kb + k < k1 && kb + k + 8 > k1) *p = last_a(a, *p, i0 + row, kb + k, k1);
-    });
-    static_for<0, NIB>([&](auto T) {
-      int kr, col;
-      place_b(decltype(T)::value, &kr, &col);
-      u32x4* p = (u32x4*)(L + A_BYTES / 2 + 512 * (NIB * wave + decltype(T)::value));
-      if (kb + kr == a.K - 1 && j0 + col < a.N && j0 + col + 8 > a.N) *p = last_b(a, *p, kb + kr, j0 + col, k1);
-    });
-    lds_wait();
-  };
-
-  floatx16 acc[TM][TN];
-#pragma unroll
-  for (int mi = 0; mi < TM; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
-  shortx8 fa[2][TM], fb[2][TN];
-  // the lane's addresses within the slabs (16-k steps: the A chunk moves
-  // under its swizzle, the B rows by a constant)
-  const int ar = wm * WTM + (lane & 31), h = lane >> 5;
-  const int vi = lane & 15, br = 8 * h + (vi >> 2), bc = wn * WTN + 16 * ((lane >> 4) & 1) + 4 * (vi & 3);
-  int ad[4], bd[TN];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) ad[j] = ar * BK + 8 * ((2 * j + h) ^ swA(ar));
-#pragma unroll
-  for (int ni = 0; ni < TN; ++ni) bd[ni] = br * BN + 8 * (((bc + 32 * ni) >> 3) ^ swB(br)) + (bc & 7);
-  // fragments of step j of the slab in slot X, into set x
-  auto read = [&](auto X, int j, int x) {
-    const uint16_t* As = ring_array<decltype(X)::value, A_BYTES + B_BYTES>();
-    const uint16_t* Bs = As + A_BYTES / 2;
-#pragma unroll
-    for (int mi = 0; mi < TM; ++mi) fa[x][mi] = *(const shortx8*)&As[ad[j] + 32 * mi * BK];
-#pragma unroll
-    for (int ni = 0; ni < TN; ++ni) {
-      const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(&Bs[bd[ni] + 16 * j * BN]));
-      const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(&Bs[bd[ni] + (16 * j + 4) * BN]));
-      fb[x][ni] = shortx8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    }
-  };
-  auto products = [&](int x) {
-#pragma unroll
-    for (int mi = 0; mi < TM; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < TN; ++ni) mfma32<F16>(acc[mi][ni], fa[x][mi], fb[x][ni]);
-  };
-
-  // prologue: slabs 0 .. NS - 2 on their way, slab 0 in, its first fragments read
-  static_for<0, NS - 1>([&](auto x) { static_for<0, NI>([&](auto t) { dma(x, x, t); }); });
-  __builtin_amdgcn_s_waitcnt(vmcnt_only((NS - 2) * NI));
-  if constexpr (UN)
-    if (nslab == 1) mend(std::integral_constant<int, 0>{});
-  ring_barrier();
-  read(std::integral_constant<int, 0>{}, 0, 0);
-  // the loads owed to the slot freed by the last barrier: slab `next`, slot
-  // (x + NS - 1) % NS, a quarter per step
-  auto slab = [&](int sl, auto X, auto MEND) {
-    constexpr int x = decltype(X)::value;
-    constexpr std::integral_constant<int, (x + 1) % NS> nxt{};
-    constexpr std::integral_constant<int, (x + NS - 1) % NS> prev{};   // slot of slab sl - 1: takes slab sl + NS - 1
-    constexpr std::integral_constant<int, (x + 2 * NS - 2) % NS> old{};  // slot of slab sl - 2: takes slab sl + NS - 2
-    static_for<0, 4>([&](auto J) {
-      constexpr int j = decltype(J)::value;
-      if constexpr (j == 3) {
-        // own loads of slab sl + 1 in (slabs sl + 2 .. sl + NS - 2 may be out), then everybody's
-        __builtin_amdgcn_s_waitcnt(vmcnt_only((NS - 3) * NI));
-        if constexpr (UN && decltype(MEND)::value)
-          if (sl + 2 == nslab) mend(nxt);
-        ring_barrier();
-        read(nxt, 0, 0);
-      } else {
-        read(X, j + 1, (j + 1) & 1);
-      }
-      products(j & 1);
-      // step 3 begins the loads of slab sl + NS - 1; steps 0 .. 2 finish those
-      // that the slab before began (the first slab has none to finish)
-      static_for<0, NI>([&](auto T) {
-        constexpr int t = decltype(T)::value, q = t * 4 / NI;   // quarter 0: step 3, then steps 0, 1, 2
-        if constexpr (j == 3) {
-          if constexpr (q == 0) dma(sl + NS - 1, prev, T);
-        } else if constexpr (q == j + 1) {
-          if (sl > 0) dma(sl + NS - 2, old, T);
-        }
-      });
-      __builtin_amdgcn_sched_barrier(0);
-    });
-  };
-  int sl = 0;   // the loop leaves 1 to NS slabs: the last one is slot 0's after it, or one of the rest's
-  for (; sl + NS < nslab; sl += NS)
-    static_for<0, NS>([&](auto x) { slab(sl + x, x, std::integral_constant<bool, decltype(x)::value == NS - 1>{}); });
-  static_for<0, NS>([&](auto x) {
-    if (sl + decltype(x)::value < nslab) slab(sl + decltype(x)::value, x, std::integral_constant<bool, decltype(x)::value != NS - 1>{});
-  });
-  __builtin_amdgcn_s_waitcnt(vmcnt_only(0));   // nothing lands in the staging area later
-  __syncthreads();
-
-  // epilogue: the block's bias as binary32 in slot 0's B array; each wave
-  // stages 16-row halves of its bands through its part of the A arrays
-  // (pitch WTN + 8 floats: the two row sets of one write 32 banks apart) and
-  // finishes four columns per store
-  constexpr int CSP = WTN + 8, CSB = 16 * CSP * 4, PER = A_BYTES / CSB;
-  static_assert(PER >= 1 && PER * NS >= NW && BN * 4 <= B_BYTES, "epilogue staging fits");
-  float* bsh = reinterpret_cast<float*>(ring_array<0, A_BYTES + B_BYTES>() + A_BYTES / 2);
-  stage_bias(a, j0, BN, bsh);
-  __syncthreads();
-  const bool bias = needs_bias(a);
-  float* cs = nullptr;
-  static_for<0, NS>([&](auto x) {
-    if (wave / PER == decltype(x)::value)
-      cs = reinterpret_cast<float*>(ring_array<decltype(x)::value, A_BYTES + B_BYTES>()) + (wave % PER) * 16 * CSP;
-  });
-#pragma unroll
-  for (int mi = 0; mi < TM; ++mi) {
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-#pragma unroll
-      for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-        for (int r = 8 * half; r < 8 * half + 8; ++r)
-          cs[(8 * (r / 4) - 16 * half + 4 * h + (r & 3)) * CSP + 32 * ni + (lane & 31)] = acc[mi][ni][r];
-      lds_wait();
-#pragma unroll 2
-      for (int q = lane; q < 16 * WTN / 4; q += 64) {
-        const int rr = q / (WTN / 4), cc = 4 * (q % (WTN / 4));
-        const int64_t gi = i0 + wm * WTM + 32 * mi + 16 * half + rr, gj = j0 + wn * WTN + cc;
-        const float4 b4 = bias ? *(const float4*)&bsh[wn * WTN + cc] : float4{0.f, 0.f, 0.f, 0.f};
-        if (gi < a.M && gj < a.N) (void)finish4v<UN>(a, s, gi, gj, *(const float4*)&cs[rr * CSP + cc], b4);
-      }
-      lds_wait();
-    }
-  }
-}
 
 template <int BM, int BN, int WM, int WN, int NS>
 static hipError_t launch_ring_t(const GemmArgs& a, bool un, hipStream_t st) {
@@ -293,7 +17,7 @@ static hipError_t launch_ring_t(const GemmArgs& a, bool un, hipStream_t st) {
 hipError_t launch_gemm_ring(const GemmArgs& a, int tm, int tn, bool un, hipStream_t st) {
   if (tm == 128 && tn == 128) return launch_ring_t<128, 128, 2, 4, 4>(a, un, st);
   if (tm == 64 && tn == 128) return launch_ring_t<64, 128, 2, 4, 4>(a, un, st);
-  if (tm == 64 && tn == 64) return launch_ring_t<64, 64, 2, 2, 6>(a, un, st);
+  if (tm == 64 && tn == 64) return launch_ring_t<64, 64, 2, 2, 5>(a, un, st);
   return hipErrorInvalidValue;
 }
 

@@ -126,10 +126,13 @@ hipError_t launch_gemm_b16n(const GemmArgs& a, hipStream_t s);
 // 2^31; the tiled layout's conditions, or odd: any size and alignment with N, K >= 8,
 // contiguous parts)
 hipError_t launch_gemm_ring(const GemmArgs& a, int tile_m, int tile_n, bool odd, hipStream_t s);
+// the same for tile chains and trees with fma = 1 (tile ends on 32-k steps from the part
+// start; part_tiles: the longest part's tiles, for a tree at most 256, on 128 x 128 blocks 8)
+hipError_t launch_gemm_ring_tiles(const GemmArgs& a, int part_tiles, int tile_m, int tile_n, bool odd, hipStream_t s);
 // the few-row (4), v3 (3) and ping-pong (5) kernels, and the tile-combine one, on
 // operands of any size and alignment (N, K >= 8; contiguous parts)
 hipError_t launch_gemm_odd(const GemmArgs& a, int kern, int tile_m, int tile_n, hipStream_t s);
-hipError_t launch_gemm_odd_tc(const GemmArgs& a, int levels, hipStream_t s);
+hipError_t launch_gemm_odd_tc(const GemmArgs& a, hipStream_t s);   // fma = 0 only
 hipError_t launch_gemm_wide(const GemmArgs& a, int tile_m, int tile_n, hipStream_t s);
 bool wide_supported(int tile_m, int tile_n);
 bool wide_is_pp(int tile_m, int tile_n);   // the ping-pong kernel (buffer-resource offsets)

@@ -1,6 +1,6 @@
 """GPU parity of the ring GEMM kernels at the edges of their blocks, slots and
 parts: every block shape, K from one chunk to one slab more than the slots
-hold and around it, parts shorter than a slab, aligned and odd, against the
+hold and around it, parts shorter than a slab, tile chains and trees, aligned and odd, against the
 generic kernel on every output and the CPU oracle on some rows, bit for bit."""
 import numpy as np
 import pytest
@@ -35,8 +35,10 @@ def device(bits, dtype, off):
 SIZES = [(33, 104), (64, 64), (65, 200), (128, 72), (3, 6408), (32, 5000), (1000, 1104), (961, 2056), (2000, 2056)]
 DESCS = [dict(), dict(out="bf16", epilogue="bias_silu", epi_round="pre_act"), dict(in_dtype="f16", out="bf16", epilogue="bias"),
          dict(split_k=3, split_combine="tree", partial="bf16", out="bf16", epilogue="bias"), dict(split_k=2, in_dtype="f16"),
-         dict(tail="first", tile_k=64)]
-KS = [8, 64, 72, 128, 192, 256, 320, 328, 384, 448, 520]
+         dict(tail="first", tile_k=64), dict(tile_combine="tree", tile_k=32), dict(tile_combine="tree", tile_k=64, out="bf16",
+         epilogue="bias_silu"), dict(tile_combine="seq", tile_k=96, in_dtype="f16"), dict(tile_combine="tree", tile_k=32,
+         in_dtype="f16", split_k=2, split_combine="tree", partial="bf16"), dict(tile_combine="seq", tile_k=32, tail="first")]
+KS = [8, 64, 72, 128, 192, 256, 320, 328, 384, 448, 520, 2080, 8192]
 
 
 @pytest.mark.parametrize("odd", [0, 1])
@@ -49,10 +51,12 @@ def test_ring(dg, di, size, odd):
     f16 = desc.get("in_dtype") == "f16"
     dt = torch.float16 if f16 else torch.bfloat16
     spread = inputs.spread_f16 if f16 else inputs.spread_bf16
-    for K in KS if size[0] < 900 else KS[di % 3::3]:
+    for K in KS if size[0] < 900 else KS[di % 3:-1:3]:
         M, N = size[0], size[1] - 3 * odd
         if desc.get("tail") != "first":
             K = K + 1 if odd else K
+        elif K % 32:
+            K = K // 32 * 32 + 32                 # a tile tree or chain starts on a 32-k step
         parts = desc.get("split_k", 1)
         if parts > 1 and (parts - 1) * (-(-K // (32 * parts)) * 32) >= K:
             continue                              # the cut plan would leave a part empty
