@@ -337,13 +337,14 @@ typedef struct {
                       nothing else: four waves on the block-scaled fp8
                       instructions, blocks tile_m x tile_n of 128 x 128,
                       256 x 256 or 256 x 128 (0: 256 x 128 from 129 rows
-                      on, else 128 x 128; no other knob;
-                      the library's choice when tile_combine is DG_CARRY,
+                      on, else 128 x 128; no other knob); taken
+                      when tile_combine is DG_CARRY,
                       fma = 1, the split contiguous, K and N multiples of
                       16, every part start and leading short tile on a
                       multiple of 16, A, B, C and bias 16-byte aligned;
                       otherwise DG_ERR_UNSUPPORTED, and kernel 0 runs the
-                      generic kernel 1).  e4m3 x e4m3 is not taken by
+                      generic kernel 1 (where it is taken, kernel 0 also has
+                      smaller blocks without a knob).  e4m3 x e4m3 is not taken by
                       dg_gemm_packed.  14 bf16 operands on kernel 13's
                       pipeline (256 x 128 blocks, two per CU, 32x32x16
                       instructions; the tiled layout's conditions; no

@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdg.so")
-SOURCES = ["dg_api.cpp", "dg_gemm.hip", "dg_gemm_odd.hip", "dg_gemm_ring.hip", "dg_gemm_ring_tiles.hip", "dg_panel.hip", "dg_rowsum.hip", "dg_rownorm.hip", "dg_rownorm_strided.hip",
+SOURCES = ["dg_api.cpp", "dg_gemm.hip", "dg_gemm_odd.hip", "dg_gemm_ring.hip", "dg_gemm_ring_tiles.hip", "dg_gemm_ring_f8.hip", "dg_panel.hip", "dg_rowsum.hip", "dg_rownorm.hip", "dg_rownorm_strided.hip",
            "dg_attn.hip", "dg_attn_split.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

@@ -156,7 +156,7 @@ bool capturing(hipStream_t st) {
 struct AutoConfig {
   int kern, tm, tn, order, occ, depth, slab_k;
 };
-constexpr int RING = 100, RING_TILES = 101;   // the ring kernels: no knobs
+constexpr int RING = 100, RING_TILES = 101, RING_F8 = 102;   // the ring kernels: no knobs
 
 // The ping-pong kernels address their operands with 31-bit byte offsets from
 // the block's first A row and the part's first B row.
@@ -216,6 +216,26 @@ void ring_config(int64_t M, int64_t N, int S, int ncu, bool tiles, bool big, int
   const bool b128 = big && c128 < c64w && c128 < c64;
   *tm = b128 ? 128 : 64;
   *tn = b128 || c64w < c64 ? 128 : 64;
+}
+
+// The same for e4m3, and whether the ring is taken at all: a round of 4096 k
+// took 18.7 us with 128 x 128 blocks, 15 with 64 x 128, 13.5 with one 64 x 64
+// block per CU and 20 with two; kernel 13's 256 x 128 blocks take 38 while
+// they are one per CU and 64 with two.  2048 x 6144 x 4096 61.6 us on kernel
+// 13, 57.3 on the ring; 1024 x 14336 x 4096 64.8 and 71.8.
+bool ring_f8_config(int64_t M, int64_t N, int S, int ncu, int* tm, int* tn) {
+  auto rounds = [&](int64_t bm, int64_t bn, int64_t per) {
+    return (double)((S * ((M + bm - 1) / bm) * ((N + bn - 1) / bn) + per - 1) / per);
+  };
+  const double k13 = rounds(256, 128, ncu) == 1 ? 38 : rounds(256, 128, 2 * ncu) * 64;
+  const double c128 = rounds(128, 128, ncu) * 18.7, c64w = rounds(64, 128, ncu) * 15;
+  const double c64 = rounds(64, 64, ncu) == 1 ? 13.5 : rounds(64, 64, 2 * ncu) * 20;
+  const bool b128 = c128 < c64w && c128 < c64;
+  *tm = b128 ? 128 : 64;
+  *tn = b128 || c64w < c64 ? 128 : 64;
+  if (std::min({c128, c64w, c64}) < k13) return true;
+  *tm = *tn = 0;
+  return false;
 }
 
 // The kernel of a product on a chunk grid.  fits: pp_fits, the offsets of the
@@ -482,6 +502,9 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
     }
     if (kern == 13 && !f8_ok) return DG_ERR_UNSUPPORTED;
     if (kern == 0) kern = f8_ok ? 13 : 1;
+    if (f8_ok && !(knobs && (knobs->kernel || tm || tn)) && M * K < 0x7fffffff && K * N < 0x7fffffff &&
+        ring_f8_config(M, N, a.S, cu_count(), &tm, &tn))
+      kern = RING_F8;
     // 256-row blocks (buffer offsets: M K and K N bytes below 2^31) from
     // 129 rows on, else 128 x 128
     if (kern == 13) {
@@ -618,6 +641,9 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
   if (kern == RING) {
     a.order = order;
     e = dg::launch_gemm_ring(a, tm, tn, odd, st);
+  } else if (kern == RING_F8) {
+    a.order = 3;
+    e = dg::launch_gemm_ring_f8(a, tm, tn, st);
   } else if (kern == RING_TILES) {
     a.order = 3;
     e = dg::launch_gemm_ring_tiles(a, (int)part_tiles, tm, tn, odd, st);

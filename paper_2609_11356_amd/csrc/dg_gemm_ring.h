@@ -1,4 +1,4 @@
-// dg_gemm_ring.h -- bf16 / binary16 GEMM on BM x BN blocks with a ring of
+// dg_gemm_ring.h -- bf16 / binary16 / e4m3 GEMM on BM x BN blocks with a ring of
 // NS LDS slots filled by direct-to-LDS loads, for the sizes between the
 // few-row kernels and the 256-row blocks: the order and bits of the other
 // chunk-grid kernels (8-k chunks in increasing k through one accumulator, on
@@ -34,6 +34,11 @@
 // tile_k 64 trees, before (gemm_tc: 128-row blocks, so that most sizes filled a
 // few CUs) and after: 256 x 4096 x 4096 70.8 -> 27.8 us, 1024 x 4096 x 4096 140
 // -> 62, 2048 x 14336 x 4096 963 -> 510, 1 x 1024 x 1024 18.9 -> 10.1.
+// EB = 1, e4m3 (128-k slabs of the same bytes, two 64-k steps): before (kernel
+// 13's 256 x 128 blocks) and after 256 x 4096 x 4096 34.6 -> 14.2 us, 1024 x 4096
+// x 4096 35.3 -> 21.7, 16 x 4096 x 14336 101 -> 35, 64 x 14336 x 4096 34.8 -> 15.3.
+// B's transposing reads take 8 rows x 32 columns per half wave, whose 16
+// chunks the swizzle puts on 16 slots.
 // UN (odd sizes): chunks are loaded where they lie, as in dg_gemm_tile.h, and
 // the lanes that loaded the last slab mend it in LDS before it is read.
 #pragma once
@@ -46,6 +51,9 @@ namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void* lds_void;
+typedef int intx2 __attribute__((ext_vector_type(2)));
+typedef int intx8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) intx2* lds_i2;
 
 // LDS array number ID of the workgroup (one per slot and operand, so that the
 // compiler can tell a read from the loads in flight).
@@ -73,13 +81,14 @@ __device__ __forceinline__ void mfma32(floatx16& c, const shortx8& a, const shor
 
 }  // namespace
 
-template <int BM, int BN, int WM, int WN, int NS, bool F16, bool UN, int COMB = DG_CARRY, int L = 1>
+template <int BM, int BN, int WM, int WN, int NS, bool F16, bool UN, int COMB = DG_CARRY, int L = 1, int EB = 2>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_ring(GemmArgs a) {
-  constexpr int NW = WM * WN, BK = 64, WTM = BM / WM, WTN = BN / WN, TM = WTM / 32, TN = WTN / 32;
-  constexpr int BROW = BN / 8, A_BYTES = BM * BK * 2, B_BYTES = BK * BN * 2;
+  // EB: bytes per element; a slab is 128 bytes of k, a step one MFMA of k
+  constexpr int NW = WM * WN, BK = 128 / EB, EPC = 16 / EB, STEPS = EB == 2 ? 4 : 2, WTM = BM / WM, WTN = BN / WN, TM = WTM / 32, TN = WTN / 32;
+  constexpr int BROW = BN / EPC, A_BYTES = BM * 128, B_BYTES = BK * BN * EB;
   constexpr int NIA = A_BYTES / 1024 / NW, NIB = B_BYTES / 1024 / NW, NI = NIA + NIB;   // loads per wave and slab
   static_assert(A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0 && TM >= 1 && TN >= 1, "whole loads and tiles");
-  static_assert((BROW == 8 || BROW == 16 || BROW == 32) && NS >= 4 && NS <= 6 && (NS - 1) * NI <= 63, "the waits fit the load counter");
+  static_assert((BROW == 4 || BROW == 8 || BROW == 16) && (EB == 2 || (!UN && COMB == DG_CARRY)) && NS >= 4 && NS <= 6 && (NS - 1) * NI <= 63, "the waits fit the load counter");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
@@ -91,7 +100,10 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2,
   const int64_t k0 = a.cuts[s], k1 = a.cuts[s + 1];
   const int nslab = (int)((k1 - k0 + BK - 1) / BK);
   auto swA = [](int r) { return (r >> 1) & 7; };
-  auto swB = [](int k) { return BROW >= 16 ? (k & 3) << 2 : ((k >> 1) & 1) << 2; };
+  auto swB = [](int k) {
+    if constexpr (EB == 1) return BROW == 8 ? ((k >> 1) & 3) << 1 : ((k >> 2) & 1) << 1;
+    else return BROW == 16 ? (k & 3) << 2 : ((k >> 1) & 1) << 2;
+  };
 
   // load t of the wave fills 1 KB: A rows 8 (NIA wave + t).., or B rows; each
   // lane fetches the chunk that belongs at its place (a row past M or a
@@ -99,13 +111,13 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2,
   constexpr uint32_t OOB = 0x80000000u;
   constexpr int BRUN = 64 / BROW;               // B rows per load
   // place of the lane's chunk of load t: A row and first k, B k row and first column
-  auto place_a = [&](int t, int* row, int* k) { *row = (NIA * wave + t) * 8 + lane / 8; *k = 8 * ((lane & 7) ^ swA(*row)); };
+  auto place_a = [&](int t, int* row, int* k) { *row = (NIA * wave + t) * 8 + lane / 8; *k = EPC * ((lane & 7) ^ swA(*row)); };
   auto place_b = [&](int u, int* kr, int* col) {
     *kr = (NIB * wave + u) * BRUN + lane / BROW;
-    *col = 8 * ((lane % BROW) ^ swB(*kr));
+    *col = EPC * ((lane % BROW) ^ swB(*kr));
   };
   // UN: the resources start on 16 bytes, mis* bytes before the operands' own start
-  const uint16_t *pA = a.A + i0 * a.K, *pB = a.B + k0 * a.N;
+  const char *pA = (const char*)a.A + i0 * a.K * EB, *pB = (const char*)a.B + k0 * a.N * EB;
   const uint32_t misA = UN ? (uint32_t)((uintptr_t)pA & 15) : 0, misB = UN ? (uint32_t)((uintptr_t)pB & 15) : 0;
   uint32_t off[NI];
   int kl[NI];   // the chunk is loaded while this k lies before the part end
@@ -113,22 +125,22 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2,
   for (int t = 0; t < NIA; ++t) {
     int row, k;
     place_a(t, &row, &k);
-    off[t] = i0 + row < a.M ? (uint32_t)((row * a.K + k) * 2) + misA : OOB;
+    off[t] = i0 + row < a.M ? (uint32_t)((row * a.K + k) * EB) + misA : OOB;
     kl[t] = UN && k1 == a.K && i0 + row == a.M - 1 ? k + 7 : k;             // the matrix's last chunk only whole
   }
 #pragma unroll
   for (int u = 0; u < NIB; ++u) {
     int kr, col;
     place_b(u, &kr, &col);
-    off[NIA + u] = j0 + col < a.N ? (uint32_t)((kr * a.N + j0 + col) * 2) + misB : OOB;
+    off[NIA + u] = j0 + col < a.N ? (uint32_t)((kr * a.N + j0 + col) * EB) + misB : OOB;
     kl[NIA + u] = UN && k1 == a.K && j0 + col + 8 > a.N ? kr + 1 : kr;
   }
-  const int64_t recA = (a.M - i0) * a.K * 2 + misA, recB = (a.K - k0) * a.N * 2 + misB;
+  const int64_t recA = (a.M - i0) * a.K * EB + misA, recB = (a.K - k0) * a.N * EB + misB;
   const __amdgpu_buffer_rsrc_t rA = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)((const char*)pA - misA), (short)0, (int)(recA < 0x7fffffff ? recA : 0x7fffffff), 0x00020000);
+      (void*)(pA - misA), (short)0, (int)(recA < 0x7fffffff ? recA : 0x7fffffff), 0x00020000);
   const __amdgpu_buffer_rsrc_t rB = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)((const char*)pB - misB), (short)0, (int)(recB < 0x7fffffff ? recB : 0x7fffffff), 0x00020000);
-  const int stepB = (int)(BK * a.N * 2);
+      (void*)(pB - misB), (short)0, (int)(recB < 0x7fffffff ? recB : 0x7fffffff), 0x00020000);
+  const int stepB = (int)(BK * a.N * EB);
   // load t of slab sl into slot X
   auto dma = [&](int sl, auto X, auto T) {
     constexpr int x = decltype(X)::value, t = decltype(T)::value;
@@ -136,7 +148,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2,
     const uint32_t o = kl[t] < left ? off[t] : OOB;
     if constexpr (t < NIA)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (lds_void)(ring_array<x, A_BYTES + B_BYTES>() + 512 * (NIA * wave + t)), 16, o,
-                                               sl < nslab ? (int)(k0 + sl * BK) * 2 : 0, 0, 0);
+                                               sl < nslab ? (int)((k0 + sl * BK) * EB) : 0, 0, 0);
     else
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           rB, (lds_void)(ring_array<x, A_BYTES + B_BYTES>() + A_BYTES / 2 + 512 * (NIB * wave + t - NIA)), 16, o, sl < nslab ? sl * stepB : 0, 0, 0);
@@ -208,34 +220,61 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2,
       });
     tile_end = last ? 0x7fffffff : tile_end + tk < len ? tile_end + tk : len;
   };
-  shortx8 fa[2][TM], fb[2][TN];
-  // the lane's addresses within the slabs (16-k steps: the A chunk moves
-  // under its swizzle, the B rows by a constant)
+  typedef std::conditional_t<EB == 2, shortx8, intx8> Frag;
+  Frag fa[2][TM], fb[2][TN];
+  // the lane's addresses within the slabs, in bytes (the A chunk moves under
+  // its swizzle, the B rows by a constant)
   const int ar = wm * WTM + (lane & 31), h = lane >> 5;
-  const int vi = lane & 15, br = 8 * h + (vi >> 2), bc = wn * WTN + 16 * ((lane >> 4) & 1) + 4 * (vi & 3);
+  const int vi = lane & 15, br = EB == 2 ? 8 * h + (vi >> 2) : 16 * h + (vi >> 1);
+  const int bc = wn * WTN + 16 * ((lane >> 4) & 1) + (EB == 2 ? 4 * (vi & 3) : 8 * (vi & 1));
   int ad[4], bd[TN];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) ad[j] = ar * BK + 8 * ((2 * j + h) ^ swA(ar));
+  for (int j = 0; j < 4; ++j) ad[j] = ar * 128 + 16 * ((2 * j + h) ^ swA(ar));
 #pragma unroll
-  for (int ni = 0; ni < TN; ++ni) bd[ni] = br * BN + 8 * (((bc + 32 * ni) >> 3) ^ swB(br)) + (bc & 7);
+  for (int ni = 0; ni < TN; ++ni) {
+    const int c = bc + 32 * ni;
+    bd[ni] = EB * br * BN + 16 * ((c / EPC) ^ swB(br)) + EB * (c % EPC);
+  }
   // fragments of step j of the slab in slot X, into set x
   auto read = [&](auto X, int j, int x) {
-    const uint16_t* As = ring_array<decltype(X)::value, A_BYTES + B_BYTES>();
-    const uint16_t* Bs = As + A_BYTES / 2;
+    const char* As = (const char*)ring_array<decltype(X)::value, A_BYTES + B_BYTES>();
+    const char* Bs = As + A_BYTES;
+    if constexpr (EB == 2) {
 #pragma unroll
-    for (int mi = 0; mi < TM; ++mi) fa[x][mi] = *(const shortx8*)&As[ad[j] + 32 * mi * BK];
+      for (int mi = 0; mi < TM; ++mi) fa[x][mi] = *(const shortx8*)&As[ad[j] + 32 * mi * 128];
 #pragma unroll
-    for (int ni = 0; ni < TN; ++ni) {
-      const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(&Bs[bd[ni] + 16 * j * BN]));
-      const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(&Bs[bd[ni] + (16 * j + 4) * BN]));
-      fb[x][ni] = shortx8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      for (int ni = 0; ni < TN; ++ni) {
+        const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(&Bs[bd[ni] + 16 * j * BN * 2]));
+        const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(&Bs[bd[ni] + (16 * j + 4) * BN * 2]));
+        fb[x][ni] = shortx8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      }
+    } else {
+      // a lane's 32 bytes: k = 16h + 0..15 and 32 + 16h + 0..15 of the step's 64
+#pragma unroll
+      for (int mi = 0; mi < TM; ++mi) {
+        const u32x4 lo = *(const u32x4*)&As[ad[2 * j] + 32 * mi * 128];
+        const u32x4 hi = *(const u32x4*)&As[ad[2 * j + 1] + 32 * mi * 128];
+        fa[x][mi] = intx8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+      }
+#pragma unroll
+      for (int ni = 0; ni < TN; ++ni) {
+        intx2 v[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+          v[p] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i2)(&Bs[bd[ni] + (64 * j + 8 * (p & 1) + 32 * (p >> 1)) * BN]));
+        fb[x][ni] = intx8{v[0][0], v[0][1], v[1][0], v[1][1], v[2][0], v[2][1], v[3][0], v[3][1]};
+      }
     }
   };
   auto products = [&](int x) {
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
-      for (int ni = 0; ni < TN; ++ni) mfma32<F16>(acc[mi][ni], fa[x][mi], fb[x][ni]);
+      for (int ni = 0; ni < TN; ++ni) {
+        if constexpr (EB == 2) mfma32<F16>(acc[mi][ni], fa[x][mi], fb[x][ni]);
+        else   // the block-scaled instruction with unit scales: the chain of 16-k chunks
+          acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[x][mi], fb[x][ni], acc[mi][ni], 0, 0, 0, 127, 0, 127);
+      }
   };
 
   // prologue: slabs 0 .. NS - 2 on their way, slab 0 in, its first fragments read
@@ -246,15 +285,15 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2,
   ring_barrier();
   read(std::integral_constant<int, 0>{}, 0, 0);
   // the loads owed to the slot freed by the last barrier: slab `next`, slot
-  // (x + NS - 1) % NS, a quarter per step
+  // (x + NS - 1) % NS, a share per step
   auto slab = [&](int sl, auto X, auto MEND) {   // MEND: slab sl + 1 may be the last
     constexpr int x = decltype(X)::value;
     constexpr std::integral_constant<int, (x + 1) % NS> nxt{};
     constexpr std::integral_constant<int, (x + NS - 1) % NS> prev{};   // slot of slab sl - 1: takes slab sl + NS - 1
     constexpr std::integral_constant<int, (x + 2 * NS - 2) % NS> old{};  // slot of slab sl - 2: takes slab sl + NS - 2
-    static_for<0, 4>([&](auto J) {
+    static_for<0, STEPS>([&](auto J) {
       constexpr int j = decltype(J)::value;
-      if constexpr (j == 3) {
+      if constexpr (j == STEPS - 1) {
         // own loads of slab sl + 1 in (slabs sl + 2 .. sl + NS - 2 may be out), then everybody's
         __builtin_amdgcn_s_waitcnt(vmcnt_only((NS - 3) * NI));
         if constexpr (UN && decltype(MEND)::value)
@@ -267,11 +306,11 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2,
       products(j & 1);
       if constexpr (COMB != DG_CARRY && (j & 1))   // every tile ends on a 32-k step, or the part does
         if (64 * sl + 16 * j + 16 >= tile_end) close_tile();
-      // step 3 begins the loads of slab sl + NS - 1; steps 0 .. 2 finish those
+      // the last step begins the loads of slab sl + NS - 1; the others finish those
       // that the slab before began (the first slab has none to finish)
       static_for<0, NI>([&](auto T) {
-        constexpr int t = decltype(T)::value, q = t * 4 / NI;   // quarter 0: step 3, then steps 0, 1, 2
-        if constexpr (j == 3) {
+        constexpr int t = decltype(T)::value, q = t * STEPS / NI;   // the first with this slab's last step
+        if constexpr (j == STEPS - 1) {
           if constexpr (q == 0) dma(sl + NS - 1, prev, T);
         } else if constexpr (q == j + 1) {
           if (sl > 0) dma(sl + NS - 2, old, T);

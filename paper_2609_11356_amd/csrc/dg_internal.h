@@ -129,6 +129,8 @@ hipError_t launch_gemm_ring(const GemmArgs& a, int tile_m, int tile_n, bool odd,
 // the same for tile chains and trees with fma = 1 (tile ends on 32-k steps from the part
 // start; part_tiles: the longest part's tiles, for a tree at most 256, on 128 x 128 blocks 8)
 hipError_t launch_gemm_ring_tiles(const GemmArgs& a, int part_tiles, int tile_m, int tile_n, bool odd, hipStream_t s);
+// the same blocks for e4m3 x e4m3 (launch_gemm_f8's conditions, M K and K N below 2^31)
+hipError_t launch_gemm_ring_f8(const GemmArgs& a, int tile_m, int tile_n, hipStream_t s);
 // the few-row (4), v3 (3) and ping-pong (5) kernels, and the tile-combine one, on
 // operands of any size and alignment (N, K >= 8; contiguous parts)
 hipError_t launch_gemm_odd(const GemmArgs& a, int kern, int tile_m, int tile_n, hipStream_t s);

@@ -1,5 +1,5 @@
 """GPU parity of the ring GEMM kernels at the edges of their blocks, slots and
-parts: every block shape, K from one chunk to one slab more than the slots
+parts: every block shape, operand type, K from one chunk to one slab more than the slots
 hold and around it, parts shorter than a slab, tile chains and trees, aligned and odd, against the
 generic kernel on every output and the CPU oracle on some rows, bit for bit."""
 import numpy as np
@@ -79,3 +79,34 @@ def test_ring(dg, di, size, odd):
         rows = np.unique([0, M // 3, M // 2, M - 1])
         assert_bits_equal(host_bits(C)[rows], oracle.gemm(desc, A[rows], B, bias), "M %d N %d K %d %s" % (M, N, K, desc))
         assert (buf[:8 + odd] == 7).all() and (buf[8 + odd + M * N:] == 7).all()   # nothing written outside
+
+
+@pytest.mark.parametrize("size", [(33, 112), (64, 64), (65, 208), (3, 6416), (1000, 1104), (961, 2064), (2000, 2064)])
+@pytest.mark.parametrize("desc", [dict(), dict(out="bf16", epilogue="bias_silu"), dict(split_k=3, split_combine="tree", out="bf16"),
+                                  dict(tail="first", tile_k=64)])
+def test_ring_e4m3(dg, desc, size):
+    import torch
+    desc = dict(dict(tile_k=32, mma="16x16x32_fp8", in_dtype="e4m3"), **desc)
+    M, N = size
+    for K in (16, 64, 128, 144, 512, 640, 656, 784, 1040):
+        parts = desc.get("split_k", 1)
+        if parts > 1 and (parts - 1) * (-(-K // (32 * parts)) * 32) >= K:
+            continue
+        rng = np.random.default_rng(M + N + K)
+        A, B = (rng.integers(0, 256, n, dtype=np.uint8) & 0xF7 for n in ((M, K), (K, N)))   # every sign and exponent, no NaN
+        A[M // 2, 0] = B[K // 2, 5] = 0x7F                                                 # a NaN row and column
+        bias = inputs.normal_bf16(M + 2, (N,), 1.0) if "epilogue" in desc else None
+        print("size %s K %d desc %s" % ((M, N), K, desc), flush=True)
+        dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+        db = None if bias is None else device(bias, torch.bfloat16, 0)
+        ct = torch.bfloat16 if desc.get("out") == "bf16" else torch.float32
+        buf, ref = torch.full((M * N + 16,), 7.0, dtype=ct, device="cuda"), torch.empty((M, N), dtype=ct, device="cuda")
+        C = buf[8:8 + M * N].view(M, N)
+        d = dg.Desc(**desc)
+        dg.dg_gemm(d, dA, dB, db, C)
+        dg.dg_gemm(d, dA, dB, db, ref, knobs=dict(kernel=1))
+        torch.cuda.synchronize()
+        assert_bits_equal(host_bits(C), host_bits(ref), "M %d N %d K %d %s" % (M, N, K, desc))
+        rows = np.unique([0, M // 3, M // 2, M - 1])
+        assert_bits_equal(host_bits(C)[rows], oracle.gemm(desc, A[rows], B, bias), "M %d N %d K %d %s" % (M, N, K, desc))
+        assert (buf[:8] == 7).all() and (buf[8 + M * N:] == 7).all()
