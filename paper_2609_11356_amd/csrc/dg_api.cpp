@@ -458,6 +458,8 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
   a.out_bf16 = p.out_dtype == DG_BF16;
   a.epilogue = p.epilogue;
   a.pre_act = p.epi_round == DG_ROUND_PRE_ACT;
+  a.split_combine = p.split_combine;
+  a.merge_bf16 = p.merge_dtype == DG_BF16;
   a.in_f16 = f16;
   a.b_e4m3 = b8;
   a.ab_e4m3 = f8;
@@ -485,8 +487,14 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
       return DG_ERR_UNSUPPORTED;
     panel_tms = tm ? tm / 16 : (M <= 16 ? 1 : M <= 32 ? 2 : 4);
     panel_avec = K % 8 == 0 && aligned(A, 16);
-    panel_depth = depth ? depth : dg::panel_default_depth(panel_tms, panel_avec, b8);
-    if (!dg::panel_supported(panel_tms, panel_depth, panel_avec, b8)) return DG_ERR_UNSUPPORTED;
+    panel_depth = depth ? depth : dg::panel_default_depth(panel_tms, b8);
+    if (panel_avec || !depth) {
+      if (!dg::panel_supported(panel_tms, panel_depth, b8)) return DG_ERR_UNSUPPORTED;
+    } else {
+      // the one depth that the knob has ever had without 16-byte A rows: the library's own
+      if (panel_tms * depth != 4 || (panel_tms != 1 && panel_tms != 2 && panel_tms != 4)) return DG_ERR_UNSUPPORTED;
+      panel_depth = dg::panel_default_depth(panel_tms, b8);
+    }
   }
 
   // The fp8 tiled kernel: a carried accumulator with fma = 1 (the 16-k chunk
@@ -637,6 +645,7 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
     a.colsum_part = colsum_part;
     *fused = true;
   }
+  bool panel_merge = false;   // the packed kernel merges the parts itself
   hipError_t e;
   if (kern == RING) {
     a.order = order;
@@ -651,7 +660,8 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
     a.order = kern == 12 ? 1 : order;
     e = kern == 12 ? dg::launch_gemm_odd_tc(a, st) : dg::launch_gemm_odd(a, kern, tm, tn, st);
   } else if (kern == 11) {
-    e = dg::launch_gemm_panel(a, panel_tms, panel_depth, panel_avec, st);
+    panel_merge = dg::panel_merges(a, panel_tms, panel_depth, cu_count());
+    e = dg::launch_gemm_panel(a, panel_tms, panel_depth, panel_avec, panel_merge, st);
   } else if (kern == 14) {
     if (((M + 255) / 256) * ((N + 127) / 128) > INT32_MAX) return DG_ERR_SHAPE;
     a.order = 1;
@@ -733,7 +743,7 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
     e = dg::launch_gemm_generic(a, st);
   }
   if (e != hipSuccess) return DG_ERR_HIP;
-  if (a.S > 1) {
+  if (a.S > 1 && !panel_merge) {
     dg::CombineArgs c;
     c.ws = a.ws;
     c.bias = a.bias;

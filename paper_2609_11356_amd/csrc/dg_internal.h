@@ -31,6 +31,7 @@ struct GemmArgs {
   int32_t S;
   int32_t tile_k, group, tile_combine, tail_first, fma;
   int32_t partial_bf16, out_bf16, epilogue, pre_act;
+  int32_t split_combine, merge_bf16;   // the merge of the parts, where a kernel does it itself
   int32_t order;                 // block order of the v3 kernels (speed only)
   int64_t split_w;               // strided split: dealt tile width (0: contiguous parts)
   int64_t n_split;               // mixed-width ping-pong: first column of the 192-wide blocks
@@ -150,9 +151,11 @@ hipError_t launch_gemm_skinny_dma(const GemmArgs& a, int tile_m, int tile_n, int
 // as 16-byte runs, else element by element)
 hipError_t launch_pack_b(const uint16_t* B, uint16_t* Bp, int64_t K, int64_t N, hipStream_t s);
 hipError_t launch_pack_b8(const uint8_t* B, uint8_t* Bp, int64_t K, int64_t N, hipStream_t s);
-hipError_t launch_gemm_panel(const GemmArgs& a, int tms, int depth, bool avec, hipStream_t s);
-bool panel_supported(int tms, int depth, bool avec, bool b8);
-int panel_default_depth(int tms, bool avec, bool b8);
+hipError_t launch_gemm_panel(const GemmArgs& a, int tms, int depth, bool avec, bool merge, hipStream_t s);
+bool panel_supported(int tms, int depth, bool b8);
+int panel_default_depth(int tms, bool b8);
+// whether it writes C itself for these parts (else partials for launch_splitk_combine)
+bool panel_merges(const GemmArgs& a, int tms, int depth, int ncu);
 bool skinny_dma_supported(int tile_m, int tile_n, int slots, int slab_k);
 hipError_t launch_splitk_combine(const CombineArgs& a, hipStream_t s);
 hipError_t launch_rowsum(const RowsumArgs& a, hipStream_t s);

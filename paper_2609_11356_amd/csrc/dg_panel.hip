@@ -32,6 +32,7 @@
 // with the part's conversion instruction (exact) just before the bf16
 // instruction, so the order and bits are those of the bf16 GEMM on the
 // widened B, with half the bytes streamed.
+#include <algorithm>
 #include <type_traits>
 
 #include "dg_device.h"
@@ -44,15 +45,16 @@ namespace {
 
 constexpr uint32_t kOOB = 0x80000000u;   // a buffer offset past any record: reads zero
 
-// 8 values of one A row from k on, each checked against K (rows whose 16-byte
-// runs are not 16-byte aligned: K % 8 != 0 or A itself unaligned).
-__device__ __forceinline__ u32x4 load_a_elems(__amdgpu_buffer_rsrc_t r, int64_t row_off, int64_t k, int64_t K,
+// 8 values of one A row from k on, each checked against K (the block that K
+// cuts short, where A's rows do not lie on 16 bytes); mis: the bytes between
+// the resource's start and A's.
+__device__ __forceinline__ u32x4 load_a_elems(__amdgpu_buffer_rsrc_t r, uint32_t mis, int64_t row_off, int64_t k, int64_t K,
                                               bool row_ok) {
   uint32_t w[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const uint32_t o0 = (row_ok && k + 2 * e < K) ? (uint32_t)((row_off + k + 2 * e) * 2) : kOOB;
-    const uint32_t o1 = (row_ok && k + 2 * e + 1 < K) ? (uint32_t)((row_off + k + 2 * e + 1) * 2) : kOOB;
+    const uint32_t o0 = (row_ok && k + 2 * e < K) ? (uint32_t)((row_off + k + 2 * e) * 2) + mis : kOOB;
+    const uint32_t o1 = (row_ok && k + 2 * e + 1 < K) ? (uint32_t)((row_off + k + 2 * e + 1) * 2) + mis : kOOB;
     const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(r, o0, 0, 0);
     const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b16(r, o1, 0, 0);
     w[e] = (lo & 0xffffu) | (hi << 16);
@@ -65,16 +67,24 @@ __device__ __forceinline__ u32x4 load_a_elems(__amdgpu_buffer_rsrc_t r, int64_t 
 // BT: the B operand, 0 bf16, 1 binary16 (A binary16 too), 2 OCP e4m3 bytes
 // (1 KB runs of two blocks, widened to bf16 before the instruction).  The
 // ring holds D runs (BPR blocks each) with the A fragments of their blocks.
-template <int TMS, int D, bool AVEC, bool STRIDED, int BT>
-__global__ __launch_bounds__(64) void gemm_panel(GemmArgs a) {
+// AVEC: A's rows lie on 16 bytes.  Otherwise a lane's 16 bytes are loaded where
+// they lie, all but those of a last block that K cuts short, whose elements
+// are loaded one by one after the ring (element loads throughout, eight a
+// block and row instead of one, took 277 us at 45 x 5816 x 12713 with eight parts
+// and an e4m3 B).
+// FUSE: the workgroup's waves are the S <= 8 parts of one panel, and the
+// partials meet in LDS in the merge's order instead of in a workspace that a
+// second launch reads.
+template <int TMS, int D, bool AVEC, bool STRIDED, int BT, bool FUSE>
+__global__ __launch_bounds__(FUSE ? 512 : 64) void gemm_panel(GemmArgs a) {
   constexpr bool F16 = BT == 1;
   constexpr int BPR = BT == 2 ? 2 : 1;         // k blocks per 1 KB run
   constexpr int RUN = 1024;
-  static_assert(!AVEC || (D - 1) * (1 + BPR * TMS) <= 63, "the ring's waits fit the load counter");
-  const int lane = threadIdx.x;
+  static_assert((D - 1) * (1 + BPR * TMS) <= 63, "the ring's waits fit the load counter");
+  const int lane = threadIdx.x & 63;
   const int64_t panel = blockIdx.x;
   const int64_t i0 = (int64_t)blockIdx.y * 16 * TMS, j0 = panel * 16;
-  const int s = blockIdx.z;
+  const int s = FUSE ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : blockIdx.z;
   // every k block index and byte offset fits 31 bits (the host keeps the
   // packed B under 2 GiB and A's rows under 2 GiB)
   const int KR = (int)((a.K + 32 * BPR - 1) / (32 * BPR)), K = (int)a.K;
@@ -92,9 +102,11 @@ __global__ __launch_bounds__(64) void gemm_panel(GemmArgs a) {
     nf = (int)((a.cuts[s + 1] + 31) / 32) - BPR * r0;
   }
   const int nr = (nf + BPR - 1) / BPR;
-  const int64_t recA = (a.M - i0) * a.K * 2, recB = ((a.N + 15) / 16) * (int64_t)KR * RUN;
+  // the resource starts on 16 bytes, misA bytes before A's own start
+  const uint32_t misA = AVEC ? 0 : (uint32_t)((uintptr_t)(a.A + i0 * a.K) & 15);
+  const int64_t recA = (a.M - i0) * a.K * 2 + misA, recB = ((a.N + 15) / 16) * (int64_t)KR * RUN;
   const __amdgpu_buffer_rsrc_t rA = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(a.A + i0 * a.K), (short)0, (int)(recA < 0x7fffffff ? recA : 0x7fffffff), 0x00020000);
+      (void*)((const char*)(a.A + i0 * a.K) - misA), (short)0, (int)(recA < 0x7fffffff ? recA : 0x7fffffff), 0x00020000);
   // the panel's runs: a base moved to the panel, the run in the scalar offset
   const __amdgpu_buffer_rsrc_t rB = __builtin_amdgcn_make_buffer_rsrc((void*)a.B, (short)0, (int)recB, 0x00020000);
   const int kl = 8 * (lane >> 4);   // the lane's first k within a block
@@ -102,12 +114,12 @@ __global__ __launch_bounds__(64) void gemm_panel(GemmArgs a) {
   // first block whose 8 k of this lane lie at or past K (only the last block
   // when K % 32 != 0).  A block's offset goes in the scalar buffer offset.
   const uint32_t vb = (uint32_t)(panel * KR * RUN) + (uint32_t)lane * 16;
-  const int flim = (K - kl + 31) / 32;
+  const int flim = AVEC ? (K - kl + 31) / 32 : K / 32;
   uint32_t va[TMS];
 #pragma unroll
   for (int mi = 0; mi < TMS; ++mi) {
     const int row = 16 * mi + (lane & 15);
-    va[mi] = (i0 + row < a.M) ? (uint32_t)((row * K + kl) * 2) : kOOB;
+    va[mi] = (i0 + row < a.M) ? (uint32_t)((row * K + kl) * 2) + misA : kOOB;
   }
   // runs g < nre are real (a strided part's last dealt tile may run past
   // K's last run: those runs read as zeros)
@@ -130,21 +142,26 @@ __global__ __launch_bounds__(64) void gemm_panel(GemmArgs a) {
     for (int h = 0; h < BPR; ++h) {
       const int f = BPR * so + h;
 #pragma unroll
-      for (int mi = 0; mi < TMS; ++mi) {
-        if constexpr (AVEC) {
-          ra[u][h][mi] = __builtin_bit_cast(
-              u32x4, __builtin_amdgcn_raw_buffer_load_b128(rA, (ok && f < flim) ? va[mi] : kOOB, f * 64, 0));
-        } else {
-          const int row = 16 * mi + (lane & 15);
-          ra[u][h][mi] = load_a_elems(rA, (int64_t)row * a.K, (int64_t)f * 32 + kl, a.K, ok && i0 + row < a.M);
-        }
-      }
+      for (int mi = 0; mi < TMS; ++mi)
+        ra[u][h][mi] = __builtin_bit_cast(
+            u32x4, __builtin_amdgcn_raw_buffer_load_b128(rA, (ok && f < flim) ? va[mi] : kOOB, f * 64, 0));
     }
   };
 
   floatx4 acc[TMS];
 #pragma unroll
   for (int mi = 0; mi < TMS; ++mi) acc[mi] = floatx4{0.f, 0.f, 0.f, 0.f};
+  auto products = [&](const u32x4& b, int h, const u32x4* fa) {
+    u32x4 bw;
+    if constexpr (BT == 2)
+      bw = u32x4{e4m3x2_bf16x2<false>(b[2 * h]), e4m3x2_bf16x2<true>(b[2 * h]), e4m3x2_bf16x2<false>(b[2 * h + 1]),
+                 e4m3x2_bf16x2<true>(b[2 * h + 1])};
+    else
+      bw = b;
+#pragma unroll
+    for (int mi = 0; mi < TMS; ++mi)
+      acc[mi] = mfma16t<F16>(__builtin_bit_cast(shortx8, fa[mi]), __builtin_bit_cast(shortx8, bw), acc[mi]);
+  };
   // The loads stay in ring order (no scheduling across the barriers): the
   // waits count on run g's loads being older than those of g + 1.
   static_for<0, D>([&](auto u) {
@@ -155,33 +172,88 @@ __global__ __launch_bounds__(64) void gemm_panel(GemmArgs a) {
     static_for<0, D>([&](auto u) {
       const int g = base + u;
       // this run's loads are the oldest of D groups in flight
-      if constexpr (AVEC) __builtin_amdgcn_s_waitcnt(vmcnt_only((D - 1) * (1 + BPR * TMS)));
+      __builtin_amdgcn_s_waitcnt(vmcnt_only((D - 1) * (1 + BPR * TMS)));
 #pragma unroll
-      for (int h = 0; h < BPR; ++h) {
-        if (BPR * g + h < nf) {
-          u32x4 bw;
-          if constexpr (BT == 2)
-            bw = u32x4{e4m3x2_bf16x2<false>(rb[u][2 * h]), e4m3x2_bf16x2<true>(rb[u][2 * h]),
-                       e4m3x2_bf16x2<false>(rb[u][2 * h + 1]), e4m3x2_bf16x2<true>(rb[u][2 * h + 1])};
-          else
-            bw = rb[u];
-#pragma unroll
-          for (int mi = 0; mi < TMS; ++mi)
-            acc[mi] = mfma16t<F16>(__builtin_bit_cast(shortx8, ra[u][h][mi]), __builtin_bit_cast(shortx8, bw),
-                                   acc[mi]);
-        }
-      }
+      for (int h = 0; h < BPR; ++h)
+        if (BPR * g + h < nf && (AVEC || BPR * run_of(g) + h < flim)) products(rb[u], h, ra[u][h]);
       load(u, g + D);
       __builtin_amdgcn_sched_barrier(0);
     });
   }
+  if constexpr (!AVEC) {
+    // the block that K cuts short, the last of the part that holds it
+    const int f = K / 32;
+    bool mine = K % 32 != 0;
+    if constexpr (STRIDED) mine = mine && (f * 32 / (int)a.split_w) % a.S == s;
+    else mine = mine && f >= BPR * r0 && f < BPR * r0 + nf;
+    if (mine) {
+      const u32x4 b = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rB, vb, f / BPR * RUN, 0));
+      u32x4 fa[TMS];
 #pragma unroll
-  for (int mi = 0; mi < TMS; ++mi)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t i = i0 + 16 * mi + 4 * (lane >> 4) + r, j = j0 + (lane & 15);
-      if (i < a.M && j < a.N) finish(a, s, i, j, acc[mi][r]);
+      for (int mi = 0; mi < TMS; ++mi) {
+        const int row = 16 * mi + (lane & 15);
+        fa[mi] = load_a_elems(rA, misA, (int64_t)row * a.K, (int64_t)f * 32 + kl, a.K, i0 + row < a.M);
+      }
+      if (BPR == 2 && (f & 1)) products(b, BPR - 1, fa);
+      else products(b, 0, fa);
     }
+  }
+  if constexpr (!FUSE) {
+#pragma unroll
+    for (int mi = 0; mi < TMS; ++mi)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t i = i0 + 16 * mi + 4 * (lane >> 4) + r, j = j0 + (lane & 15);
+        if (i < a.M && j < a.N) finish(a, s, i, j, acc[mi][r]);
+      }
+  } else {
+    __shared__ float part[8][16 * TMS][16];
+#pragma unroll
+    for (int mi = 0; mi < TMS; ++mi)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        part[s][16 * mi + 4 * (lane >> 4) + r][lane & 15] = a.partial_bf16 ? round_bf16(acc[mi][r]) : acc[mi][r];
+    __syncthreads();
+    GemmArgs b = a;   // finish as a single part would, the partials rounded already
+    b.S = 1;
+    b.partial_bf16 = 0;
+    auto add = [&](float x, float y) {
+      const float v = x + y;
+      return a.merge_bf16 ? round_bf16(v) : v;
+    };
+    for (int q = threadIdx.x; q < 16 * TMS * 16; q += blockDim.x) {
+      const int row = q / 16, col = q % 16;
+      if (i0 + row >= a.M || j0 + col >= a.N) continue;
+      float y = 0.f;
+      if (a.split_combine == DG_SEQ) {
+        y = part[0][row][col];
+        for (int t = 1; t < a.S; ++t) y = add(y, part[t][row][col]);
+      } else {
+        // balanced tree: a binary counter's levels, folded low to high
+        float l0 = 0.f, l1 = 0.f, l2 = 0.f, l3 = 0.f;
+        for (int t = 0; t < a.S; ++t) {
+          float v = part[t][row][col];
+          if (!(t & 1)) { l0 = v; continue; }
+          v = add(l0, v);
+          if (!(t & 2)) { l1 = v; continue; }
+          v = add(l1, v);
+          if (!(t & 4)) { l2 = v; continue; }
+          l3 = add(l2, v);
+        }
+        bool have = false;
+        auto meet = [&](int lv, float x) {
+          if (!((a.S >> lv) & 1)) return;
+          y = have ? add(x, y) : x;
+          have = true;
+        };
+        meet(0, l0);
+        meet(1, l1);
+        meet(2, l2);
+        meet(3, l3);
+      }
+      finish(b, 0, i0 + row, j0 + col, y);
+    }
+  }
 }
 
 // The packed form of B (K x N, 16-bit elements, row-major): thread t writes
@@ -250,15 +322,43 @@ hipError_t launch_pack_b(const uint16_t* B, uint16_t* Bp, int64_t K, int64_t N, 
 // and its waits count up to (D - 1)(1 + 2 TMS) loads (the counter holds 63)
 constexpr bool panel_b8_fits(int tms, int d) { return 2 * d * tms <= 48 && (d - 1) * (1 + 2 * tms) <= 63; }
 
+// Ring depths measured best on MI355X (4096 x 4096 B, M = 1, 7, 32, 64);
+// an e4m3 ring's runs hold two blocks each
+constexpr int default_depth(int tms, bool b8) {
+  if (b8) return tms == 4 ? 6 : 8;
+  return tms == 4 ? 10 : 16;
+}
+int panel_default_depth(int tms, bool b8) { return default_depth(tms, b8); }
+
+// The parts meet inside the kernel where they are two to eight contiguous
+// ones, at the library's own depth: no partials, no second launch (8 x 4096 x
+// 14336 in eight parts 25.3 -> 20.4 us, 1 x 1024 x 1024 in two 11.9 -> 6.3).
+// One workgroup then reads on one CU what its parts read on f where panels
+// are few, at 40 to 70 GB/s: not where that costs more than the second launch
+// saves, some 250 KB (16 x 512 x 8192 in eight parts 11.75 us apart, 12.75
+// merged; 64 x 512 x 14336 16.3 and 58).
+bool panel_merges(const GemmArgs& a, int tms, int depth, int ncu) {
+  const bool b8 = a.b_e4m3 != 0;
+  if (a.S < 2 || a.S > 8 || a.split_w != 0 || depth != default_depth(tms, b8)) return false;
+  const double f = std::min<double>(a.S, (double)ncu / (double)(((a.N + 15) / 16) * ((a.M + 16 * tms - 1) / (16 * tms))));
+  const double kb = (double)a.K / (b8 ? 64 : 32) * (1 + (b8 ? 2 : 1) * tms);
+  return f <= 1 || kb * (1 - 1 / f) <= 250;
+}
+
 template <int TMS, int D, bool AVEC>
-static hipError_t launch_panel_t(const GemmArgs& a, hipStream_t st) {
-  dim3 grid((unsigned)((a.N + 15) / 16), (unsigned)((a.M + 16 * TMS - 1) / (16 * TMS)), (unsigned)a.S);
+static hipError_t launch_panel_t(const GemmArgs& a, bool merge, hipStream_t st) {
+  const unsigned panels = (unsigned)((a.N + 15) / 16), rows = (unsigned)((a.M + 16 * TMS - 1) / (16 * TMS));
   const bool strided = a.split_w != 0;
   const int bt = a.b_e4m3 ? 2 : a.in_f16 ? 1 : 0;
   auto go = [&](auto BT_) {
     constexpr int BT = decltype(BT_)::value;
-    if (strided) hipLaunchKernelGGL((gemm_panel<TMS, D, AVEC, true, BT>), grid, dim3(64), 0, st, a);
-    else hipLaunchKernelGGL((gemm_panel<TMS, D, AVEC, false, BT>), grid, dim3(64), 0, st, a);
+    const dim3 grid(panels, rows, (unsigned)a.S);
+    if (strided) hipLaunchKernelGGL((gemm_panel<TMS, D, AVEC, true, BT, false>), grid, dim3(64), 0, st, a);
+    else if (merge) {   // panel_merges: at the default depth
+      if constexpr (D == default_depth(TMS, BT == 2))
+        hipLaunchKernelGGL((gemm_panel<TMS, D, AVEC, false, BT, true>), dim3(panels, rows), dim3(64 * a.S), 0, st, a);
+    }
+    else hipLaunchKernelGGL((gemm_panel<TMS, D, AVEC, false, BT, false>), grid, dim3(64), 0, st, a);
   };
   if (bt == 2) {
     // two blocks per run: the rings whose A fragments fit the registers
@@ -271,41 +371,29 @@ static hipError_t launch_panel_t(const GemmArgs& a, hipStream_t st) {
 }
 
 // (rows of A per wave / 16, ring depth) pairs built, for 16-byte A runs and
-// for element loads
+// for any other A
 #define DG_PANEL_LIST(X) \
   X(1, 8) X(1, 16) X(1, 24) X(1, 32) X(2, 8) X(2, 12) X(2, 16) X(4, 6) X(4, 10)
-#define DG_PANEL_ELEM_LIST(X) X(1, 4) X(2, 2) X(4, 1)
+#define DG_PANEL_ANY_LIST(X) X(1, 8) X(1, 16) X(2, 8) X(2, 16) X(4, 6) X(4, 10)
 
-// Ring depths measured best on MI355X (4096 x 4096 B, M = 1, 7, 32, 64);
-// an e4m3 ring's runs hold two blocks each
-int panel_default_depth(int tms, bool avec, bool b8) {
-  if (!avec) return tms == 1 ? 4 : tms == 2 ? 2 : 1;
-  if (b8) return tms == 1 ? 8 : tms == 2 ? 8 : 6;
-  return tms == 1 ? 16 : tms == 2 ? 16 : 10;
-}
-
-bool panel_supported(int tms, int depth, bool avec, bool b8) {
+bool panel_supported(int tms, int depth, bool b8) {
   if (b8 && !panel_b8_fits(tms, depth)) return false;
 #define DG_PANEL_HAS(T_, D_) \
   if (tms == T_ && depth == D_) return true;
-  if (avec) {
-    DG_PANEL_LIST(DG_PANEL_HAS)
-  } else {
-    DG_PANEL_ELEM_LIST(DG_PANEL_HAS)
-  }
+  DG_PANEL_LIST(DG_PANEL_HAS)
 #undef DG_PANEL_HAS
   return false;
 }
 
-hipError_t launch_gemm_panel(const GemmArgs& a, int tms, int depth, bool avec, hipStream_t st) {
+hipError_t launch_gemm_panel(const GemmArgs& a, int tms, int depth, bool avec, bool merge, hipStream_t st) {
 #define DG_PANEL_RUN(T_, D_) \
-  if (tms == T_ && depth == D_) return launch_panel_t<T_, D_, AVEC_>(a, st);
+  if (tms == T_ && depth == D_) return launch_panel_t<T_, D_, AVEC_>(a, merge, st);
   if (avec) {
     constexpr bool AVEC_ = true;
     DG_PANEL_LIST(DG_PANEL_RUN)
   } else {
     constexpr bool AVEC_ = false;
-    DG_PANEL_ELEM_LIST(DG_PANEL_RUN)
+    DG_PANEL_ANY_LIST(DG_PANEL_RUN)
   }
 #undef DG_PANEL_RUN
   return hipErrorInvalidValue;

@@ -1,0 +1,65 @@
+"""GPU parity of the packed kernel where its parts meet inside one workgroup
+(two to eight parts, both merge orders and roundings), and where A's rows lie
+at any 2-byte address with NaN past K and past the matrix, against the CPU
+oracle, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2609_11356_amd import inputs
+from tests.gpu_util import assert_bits_equal, dev_bf16, dev_f16, host_bits
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dg():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_11356_amd import dg as _dg
+    _dg.lib()
+    return _dg
+
+
+def run(dg, desc, A, B, bias, off):
+    """The packed product with A `off` elements into a buffer of NaN patterns."""
+    import torch
+    kind = desc.get("in_dtype", "bf16")
+    buf = np.full(A.size + off + 8, 0xFFFF, np.uint16)
+    buf[off:off + A.size] = A.reshape(-1)
+    dA = (dev_f16 if kind == "f16" else dev_bf16)(buf)[off:off + A.size].view(A.shape)
+    if kind == "bf16_e4m3":
+        Bp = dg.dg_pack_b(torch.from_numpy(np.ascontiguousarray(B)).cuda())
+    else:
+        Bp = dg.dg_pack_b((dev_f16 if kind == "f16" else dev_bf16)(B))
+    C = torch.full((A.shape[0], B.shape[1]), 7.0, device="cuda",
+                   dtype=torch.bfloat16 if desc.get("out") == "bf16" else torch.float32)
+    dg.dg_gemm_packed(dg.Desc(**desc), dA, Bp, None if bias is None else dev_bf16(bias), C)
+    torch.cuda.synchronize()
+    return host_bits(C)
+
+
+@pytest.mark.parametrize("kind", ["bf16", "f16", "bf16_e4m3"])
+@pytest.mark.parametrize("S", [1, 2, 3, 5, 7, 8, 9])
+@pytest.mark.parametrize("off", [0, 1, 3])
+def test_parts_and_addresses(dg, kind, S, off):
+    rng = np.random.default_rng(S + off)
+    forms = [dict(split_combine="tree"), dict(split_combine="seq", out="bf16", epilogue="bias_silu"),
+             dict(split_combine="tree", partial="bf16", merge="bf16", out="bf16", epilogue="bias")]
+    # rows of 1 to 4 tiles, panel edges, K on and off the 32- and 64-k runs and
+    # cut inside the first and the second block of a run; 3000 k on 3 panels: apart
+    for n, (M, N, K) in enumerate([(1, 33, 64 * S + 9), (16, 16, 64 * S + 33), (17, 47, 64 * S), (40, 17, 64 * S + 63),
+                                   (64, 40, 64 * S + 32), (5, 48, 3001)]):
+        desc = dict(dict(tile_k=64, split_k=S, in_dtype=kind), **forms[n % 3])
+        if (S - 1) * (-(-K // (64 * S)) * 64) >= K:
+            K = 64 * S - 31
+        A = (inputs.spread_f16 if kind == "f16" else inputs.spread_bf16)(n + K, (M, K))
+        if kind == "bf16_e4m3":
+            B = rng.integers(0, 256, (K, N), dtype=np.uint8) & 0xF7
+        else:
+            B = (inputs.spread_f16 if kind == "f16" else inputs.spread_bf16)(n + N, (K, N))
+        A[M // 2, 0] = 0x7FFF           # the row before must not see it
+        bias = inputs.normal_bf16(n, (N,)) if "epilogue" in desc else None
+        print("packed", desc, (M, N, K), off, flush=True)
+        assert_bits_equal(run(dg, desc, A, B, bias, off), oracle.gemm(desc, A, B, bias), "%s %s" % (desc, (M, N, K)))
