@@ -45,7 +45,7 @@ WORKLOAD = ("GEMM suite: N=K=4096 M=1,7,32,128,1024,4096; decode 8x4096x14336 S=
 # (dg_pack_b, done once before timing); the same bits as the row-major call
 PACKED_MAX_M = 64
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gemm_pp_mlp_hbm_traffic.md")
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2609_11356_amd", "csrc", "dg_gemm.hip")
+KERNEL_SOURCES = ("dg_gemm.hip", "dg_gemm_tile.h")   # in csrc: the kernel and its body
 
 
 def mlp_traffic():
@@ -58,9 +58,10 @@ def mlp_traffic():
             if line.startswith("- ") and ": " in line:
                 k, v = line[2:].strip().split(": ", 1)
                 fields[k] = v.strip("` ")
-        sha = hashlib.sha256(open(KERNEL_SOURCE, "rb").read()).hexdigest()
-        if fields.get("dg_gemm.hip sha256") != sha:
-            return None
+        for name in KERNEL_SOURCES:
+            source = open(os.path.join(ROOT, "paper_2609_11356_amd", "csrc", name), "rb").read()
+            if fields.get(name + " sha256") != hashlib.sha256(source).hexdigest():
+                return None
         return float(fields["HBM bytes per launch"])
     except (OSError, KeyError, ValueError):
         return None
