@@ -188,7 +188,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2,
   floatx16 stk[NL > 0 ? NL : 1][TM][TN];
   uint32_t count = 0;                                  // tiles closed
   const int len = (int)(k1 - k0), tk = (int)(a.tile_k < len ? a.tile_k : len);
-  int tile_end = a.tail_first && len % tk ? len % tk : tk;   // of the open tile, from the part start
+  int tile_end = a.tail_first && tk > 0 && len % tk ? len % tk : tk;   // of the open tile, from the part start
   auto each = [&](auto f) {
     static_for<0, TM>([&](auto mi) { static_for<0, TN>([&](auto ni) { f(mi, ni); }); });
   };
@@ -327,9 +327,11 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2,
   });
   // the part's value: the chain's sum, or the tree's stack folded low to high
   // (acc holds the entry of level ctz(count); the set levels above meet it)
-  if constexpr (COMB == DG_SEQ) each([&](auto mi, auto ni) { acc[mi][ni] = stk[0][mi][ni]; });
+  // (an empty part, K = 0, has closed no tile: acc is its value)
+  if constexpr (COMB == DG_SEQ)
+    if (count) each([&](auto mi, auto ni) { acc[mi][ni] = stk[0][mi][ni]; });
   if constexpr (COMB == DG_TREE) {
-    const int low = __builtin_ctz(count);
+    const int low = count ? __builtin_ctz(count) : 0;
     static_for<0, NL>([&](auto lv) {
       constexpr int LV = decltype(lv)::value;
       if (LV > low && ((count >> LV) & 1u)) each([&](auto mi, auto ni) { acc[mi][ni] = stk[LV][mi][ni] + acc[mi][ni]; });

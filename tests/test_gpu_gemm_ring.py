@@ -110,3 +110,24 @@ def test_ring_e4m3(dg, desc, size):
         rows = np.unique([0, M // 3, M // 2, M - 1])
         assert_bits_equal(host_bits(C)[rows], oracle.gemm(desc, A[rows], B, bias), "M %d N %d K %d %s" % (M, N, K, desc))
         assert (buf[:8] == 7).all() and (buf[8 + M * N:] == 7).all()
+
+
+@pytest.mark.parametrize("desc", [dict(), dict(out="bf16", epilogue="bias_silu"), dict(tile_combine="tree", tile_k=64),
+                                  dict(tile_combine="seq", tile_k=64, epilogue="bias"), dict(tail="first", tile_combine="seq"),
+                                  dict(in_dtype="e4m3", mma="16x16x32_fp8")])
+def test_no_k(dg, desc):
+    """K = 0: the epilogue of zero."""
+    import torch
+    desc = dict(dict(tile_k=32), **desc)
+    for M, N in [(40, 64), (1000, 1104)]:
+        print("K 0", (M, N), desc, flush=True)
+        dt = torch.uint8 if desc.get("in_dtype") == "e4m3" else torch.bfloat16
+        A, B = torch.empty((M, 0), dtype=dt, device="cuda"), torch.empty((0, N), dtype=dt, device="cuda")
+        bias = device(inputs.normal_bf16(M, (N,), 1.0), torch.bfloat16, 0) if "epilogue" in desc else None
+        ct = torch.bfloat16 if desc.get("out") == "bf16" else torch.float32
+        C, ref = (torch.full((M, N), 7.0, dtype=ct, device="cuda") for _ in range(2))
+        d = dg.Desc(**desc)
+        dg.dg_gemm(d, A, B, bias, C)
+        dg.dg_gemm(d, A, B, bias, ref, knobs=dict(kernel=1))
+        torch.cuda.synchronize()
+        assert_bits_equal(host_bits(C), host_bits(ref), "%s %s" % ((M, N), desc))
