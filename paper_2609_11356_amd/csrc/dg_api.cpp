@@ -220,22 +220,24 @@ void ring_config(int64_t M, int64_t N, int S, int ncu, bool tiles, bool big, int
 
 // The same for e4m3, and whether the ring is taken at all: a round of 4096 k
 // took 18.7 us with 128 x 128 blocks, 15 with 64 x 128, 13.5 with one 64 x 64
-// block per CU and 20 with two; kernel 13's 256 x 128 blocks take 38 while
-// they are one per CU and 64 with two.  2048 x 6144 x 4096 61.6 us on kernel
-// 13, 57.3 on the ring; 1024 x 14336 x 4096 64.8 and 71.8.
+// block per CU and 20 with two.  Kernel 13's 256 x 128 blocks take 38 while
+// they are one per CU; with more of them it stays, because the ring's smaller
+// blocks fetch the operands more often.  Operands from HBM, kernel 13 and the
+// ring: 2048 x 4096 x 4096 (256 blocks) 51.8 and 47.2 us, 1300 x 4096 x 4096
+// 43.5 and 40.0; 1001 x 10656 x 4096 (336) 66.4 and 77.6, 2048 x 6144 x 4096
+// (384) 68.2 and 71.5, 2048 x 10656 x 4096 (672) 121 and 149.
 bool ring_f8_config(int64_t M, int64_t N, int S, int ncu, int* tm, int* tn) {
   auto rounds = [&](int64_t bm, int64_t bn, int64_t per) {
     return (double)((S * ((M + bm - 1) / bm) * ((N + bn - 1) / bn) + per - 1) / per);
   };
-  const double k13 = rounds(256, 128, ncu) == 1 ? 38 : rounds(256, 128, 2 * ncu) * 64;
+  if (rounds(256, 128, ncu) > 1) return false;
   const double c128 = rounds(128, 128, ncu) * 18.7, c64w = rounds(64, 128, ncu) * 15;
   const double c64 = rounds(64, 64, ncu) == 1 ? 13.5 : rounds(64, 64, 2 * ncu) * 20;
+  if (std::min({c128, c64w, c64}) >= 38) return false;
   const bool b128 = c128 < c64w && c128 < c64;
   *tm = b128 ? 128 : 64;
   *tn = b128 || c64w < c64 ? 128 : 64;
-  if (std::min({c128, c64w, c64}) < k13) return true;
-  *tm = *tn = 0;
-  return false;
+  return true;
 }
 
 // The kernel of a product on a chunk grid.  fits: pp_fits, the offsets of the
