@@ -255,9 +255,11 @@ AutoConfig auto_config(int64_t M, int64_t N, int S, int ncu, bool fits) {
   }
   // 256 x 256 blocks, each XCD given a contiguous range of them (2-3 % over
   // row-major order at 4096 x 4096 x 4096 on MI355X), where they fill three
-  // quarters of the chip: 4096 x 4096 x 4096 117 us (the ring 132); below,
-  // 2560 x 4096 x 4096 (160 blocks) 112 (the ring 90)
-  if (tiles(256, 256) >= 192) return {5, 256, 256, 3, 0, 0, 0};
+  // quarters of the chip: 4096 x 4096 x 4096 117 us (the ring 132), or where
+  // the ring's 128 x 128 blocks would take a third round: with cold operands
+  // 1001 x 10656 x 4096 94.9 us (the ring 123.6), 1300 x 6144 x 2048 48.6
+  // (63.1), 2300 x 4096 x 8192 172 (181), 2560 x 4607 x 4095 152 (164)
+  if (tiles(256, 256) >= 192 || tiles(128, 128) > 2 * ncu) return {5, 256, 256, 3, 0, 0, 0};
   AutoConfig c = {RING, 0, 0, 3, 0, 0, 0};
   ring_config(M, N, S, ncu, false, true, &c.tm, &c.tn);
   return c;

@@ -131,3 +131,22 @@ def test_no_k(dg, desc):
         dg.dg_gemm(d, A, B, bias, ref, knobs=dict(kernel=1))
         torch.cuda.synchronize()
         assert_bits_equal(host_bits(C), host_bits(ref), "%s %s" % ((M, N), desc))
+
+
+@pytest.mark.parametrize("size", [(1300, 6144, 320), (1001, 10656, 72), (2048, 4616, 264), (2300, 4101, 263), (1001, 10655, 201)])
+@pytest.mark.parametrize("desc", [dict(out="bf16", epilogue="bias_silu"), dict()])
+def test_third_round(dg, desc, size):
+    """Sizes whose 128 x 128 blocks would take a third round of the chip: the
+    256-row blocks, against the generic kernel's bits."""
+    import torch
+    M, N, K = size
+    print("size", size, desc, flush=True)
+    A, B = (device(inputs.normal_bf16(M + i, n, 1.0), torch.bfloat16, 0) for i, n in enumerate([(M, K), (K, N)]))
+    bias = device(inputs.normal_bf16(N, (N,), 1.0), torch.bfloat16, 0) if "epilogue" in desc else None
+    ct = torch.bfloat16 if desc.get("out") == "bf16" else torch.float32
+    C, ref = (torch.full((M, N), 7.0, dtype=ct, device="cuda") for _ in range(2))
+    d = dg.Desc(tile_k=64, **desc)
+    dg.dg_gemm(d, A, B, bias, C)
+    dg.dg_gemm(d, A, B, bias, ref, knobs=dict(kernel=1))
+    torch.cuda.synchronize()
+    assert_bits_equal(host_bits(C), host_bits(ref), "%s %s" % (size, desc))
