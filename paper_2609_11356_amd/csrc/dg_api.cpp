@@ -898,9 +898,8 @@ static dg::RowsumArgs rowsum_args(const dg_desc* d, const float* X, float* out, 
 // rows start off the one-wave kernel's vector loads (1 x 100001: 8.8 against
 // 224 us).
 static bool rowsum_over_waves(const dg::RowsumArgs& a) {
-  if (!dg::row_fused_ok(a, dg::ROW_SUM, a.rows, a.cols)) return false;
-  if (!a.strided && (a.cols % 4 || !aligned(a.X, 16))) return true;
-  return a.rows < 1024 && a.cols > 8192;
+  if (!(a.rows < 1024 && a.cols > 8192) && (a.strided || (a.cols % 4 == 0 && aligned(a.X, 16)))) return false;
+  return dg::row_fused_ok(a, dg::ROW_SUM, a.rows, a.cols, cu_count());
 }
 
 dg_status dg_rowsum(const dg_desc* d, const float* X, float* out, int64_t rows, int64_t cols,
@@ -954,7 +953,7 @@ dg_status dg_softmax(const dg_desc* d, const float* X, void* Y, int64_t rows, in
     if (dg::launch_softmax_split(n, (float*)ws, st) != hipSuccess) return DG_ERR_HIP;
     return DG_OK;
   }
-  if (dg::row_fused_ok(a, dg::ROW_SMX, rows, cols)) {
+  if (dg::row_fused_ok(a, dg::ROW_SMX, rows, cols, cu_count())) {
     if (dg::launch_row_fused(a, n, dg::ROW_SMX, st) != hipSuccess) return DG_ERR_HIP;
     return DG_OK;
   }
@@ -1006,7 +1005,7 @@ dg_status dg_layernorm(const dg_desc* d, const float* X, const void* w, const vo
     if (dg::launch_layernorm_fused(a, n, st) != hipSuccess) return DG_ERR_HIP;
     return DG_OK;
   }
-  if (dg::row_fused_ok(a, dg::ROW_LN, rows, cols)) {
+  if (dg::row_fused_ok(a, dg::ROW_LN, rows, cols, cu_count())) {
     if (dg::launch_row_fused(a, n, dg::ROW_LN, st) != hipSuccess) return DG_ERR_HIP;
     return DG_OK;
   }
@@ -1066,7 +1065,7 @@ dg_status dg_rmsnorm(const dg_desc* d, const float* X, const void* w, float eps,
     if (dg::launch_rmsnorm_fused(a, n, st) != hipSuccess) return DG_ERR_HIP;
     return DG_OK;
   }
-  if (dg::row_fused_ok(a, dg::ROW_RMS, rows, cols)) {
+  if (dg::row_fused_ok(a, dg::ROW_RMS, rows, cols, cu_count())) {
     if (dg::launch_row_fused(a, n, dg::ROW_RMS, st) != hipSuccess) return DG_ERR_HIP;
     return DG_OK;
   }

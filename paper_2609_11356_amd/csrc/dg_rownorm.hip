@@ -23,7 +23,8 @@
 // go in vectors whatever the row's alignment (4-byte aligned vector loads).
 //
 // Measured on MI355X (host-timed back to back, bf16 out) against the two to
-// four passes through a workspace that they replace: layer norm 4096 x 4096
+// four passes through a workspace, which stay where they are the faster
+// (row_fused_ok): layer norm 4096 x 4096
 // 25.1 us (4.0 TB/s) from 82.8, 64 x 32768 12.3 from 107; softmax 4096 x 16384
 // 93 us (4.3 TB/s) from 314, 64 x 100000 26 from 322; RMS norm 16384 x 4096
 // 100 us from 127; row sums of 64 x 32768 7.7 us from 18.6.
@@ -469,19 +470,77 @@ extern template hipError_t launch_row_fused_w<64>(const RowsumArgs&, const NormA
 extern template hipError_t launch_row_fused_w<128>(const RowsumArgs&, const NormArgs&, int, hipStream_t);
 extern template hipError_t launch_row_fused_w<256>(const RowsumArgs&, const NormArgs&, int, hipStream_t);
 
-// Contiguous leaves of 64 or 64, 128, 256 strided lanes, any alignment and
-// length up to the pass roots LDS holds; squares by the fused square-add.
-// Rows past 65536 elements are read again for each phase: once there are rows
-// enough for the passes of dg_rowsum.hip to fill the chip as well, an RMS norm
-// (one read more either way) and a layer norm over 64 lanes (whose chains the
-// eight waves fold in turn) stay on those (1000 x 131072: 277 us against 299,
-// 871 against 927).
-bool row_fused_ok(const RowsumArgs& r, int kind, int64_t rows, int64_t cols) {
+// Whether a call runs here (speed only: the kernels of dg_rowsum.hip, one wave
+// per row in one to four launches, give the same bits).  Contiguous leaves of
+// 64 or 64, 128, 256 strided lanes, any alignment and length up to the pass
+// roots LDS holds; squares by the fused square-add.
+//
+// Where both can run, the lines below are where the two cross on MI355X
+// (operands from HBM, bf16 out, us, one wave a row -> here).  A row of np
+// passes holds the 1, 4 or 16 waves it is built for whatever np is, and over
+// strided lanes the waves fold in turn, so the cost here is per row and round
+// of the chip (256 rows of 5 to 16 passes, or of more); there it is per
+// element, and several times higher where a row starts off the vector loads
+// (`al` false).
+bool row_fused_ok(const RowsumArgs& r, int kind, int64_t rows, int64_t cols, int ncu) {
   if (cols < 1 || cols > (int64_t)MAX_PASSES * PASS) return false;
   if ((kind == ROW_RMS || kind == ROW_LN || r.sumsq) && !r.fma) return false;
-  if (cols > 16 * PASS && rows >= 512 && (kind == ROW_RMS || (kind == ROW_LN && r.strided && r.leaf_w == 64)))
-    return false;
-  return r.strided ? (r.leaf_w == 64 || r.leaf_w == 128 || r.leaf_w == 256) : r.leaf_w == 64;
+  if (r.strided ? (r.leaf_w != 64 && r.leaf_w != 128 && r.leaf_w != 256) : r.leaf_w != 64) return false;
+  const int64_t np = (cols + PASS - 1) / PASS, rounds = (rows + ncu - 1) / ncu;
+  const bool al = cols % 4 == 0 && ((uintptr_t)r.X & 15) == 0, full = cols % PASS == 0;
+  const int W = r.strided ? r.leaf_w : 0;
+  // Rows past 65536 elements are read again for each phase: once there are rows
+  // enough for the other path to fill the chip as well, an RMS norm (one read
+  // more either way) and a layer norm over 64 lanes stay there (1000 x 131072:
+  // 277 against 299, 871 against 927).
+  if (np > 16 && rows >= 512 && (kind == ROW_RMS || (kind == ROW_LN && W == 64))) return false;
+  if (W == 0) {
+    // an RMS norm of aligned short rows is two short launches there: 1000 x 640
+    // 7.5 -> 8.0, 2000 x 768 8.3 -> 9.5, 64 x 3000 7.4 -> 8.4; fewer rows or
+    // more, 1 x 640 7.0 -> 6.3, 4096 x 1000 14.5 -> 12.7, 2000 x 3000 15.1 -> 13.8
+    return !(kind == ROW_RMS && al && cols < PASS &&
+             ((cols <= 1024 && rows > ncu && rows <= 8 * ncu) || (cols > 2048 && rows > 4 && rows <= 2 * ncu)));
+  }
+  if (np == 1) {
+    // (unaligned: aligned rows have their own kernels)  a wave here walks all 64
+    // slots however short the row: 16384 x 65 over 128 lanes RMS norm 11.4 ->
+    // 25.5, softmax 25 -> 38, layer norm 23 -> 31; 1000 x 65 7.0 -> 6.4, 9.6 -> 7.4,
+    // 12.5 -> 7.8.  Over 64 lanes both take as long.
+    if (W == 64) return true;
+    if (kind == ROW_RMS) return !(cols < 768 && rows > (cols < 512 ? 8 : 16) * (int64_t)ncu);
+    if (kind == ROW_LN) return !(cols < 192 && rows > 16 * (int64_t)ncu);
+    if (kind == ROW_SMX) return !(cols < 256 && rows > 8 * (int64_t)ncu);
+    return true;
+  }
+  if (kind == ROW_SMX) return true;   // three launches there
+  // layer norm: over 64 lanes the longest turns: 1500 x 24576 193 -> 247, 768 x 24576 118 -> 119
+  if (kind == ROW_LN) return !(W == 64 && np >= 5 && np <= 8 && rounds > 3 && !(np == 5 && !al));
+  if (kind == ROW_SUM) {
+    // one launch either way.  256 lanes: 256 x 32769 17 -> 12, 400 x 32769 20 ->
+    // 22, 768 x 32769 26 -> 39, 400 x 65536 33 -> 28; 64 lanes: 768 x 32768 33 -> 23,
+    // 1000 x 40000 37 -> 50
+    if (np <= 4) return true;
+    if (rounds <= 1) return rows > 1 || np > 5;
+    if (rounds == 2) return W < 256 || full || np >= 10;
+    if (rounds == 3 && W == 64 && np > 5) return true;
+    return W < 256 && full;
+  }
+  // RMS norm: two launches there.  64 lanes: 128 x 32768 40 -> 30, 512 x 32768 53
+  // -> 64, 1000 x 20000 42 -> 99, 500 x 32769 93 -> 63; 128 lanes: 256 x 20000 27 ->
+  // 19, 1000 x 20000 42 -> 65, 1000 x 32769 113 -> 96; 256 lanes: 500 x 20000 29 ->
+  // 26, 1000 x 20000 41 -> 49, 1000 x 32768 65 -> 62
+  if (np > 16) {
+    if (!al) return true;
+    return W == 64 ? rows <= 32 : rounds <= 1 || (W == 256 && np >= 21);
+  }
+  if (np <= 4) {
+    if (W == 64) return !al || (full && rows > 1 && rounds <= 4);
+    return !(al && W == 128 && rows < 4);
+  }
+  if (!al) return W == 64 ? rounds <= (np <= 8 ? 2 : 3) : W == 128 ? rounds <= 3 || np > 8 : true;
+  if (W == 64) return (rounds <= 1 && (rows > 1 || np > 5)) || (rounds == 2 && np >= 12);
+  if (W == 128) return rounds <= 1 || (rounds == 2 && (full || np > 8)) || np >= 12;
+  return rounds <= 2 || np >= 8;
 }
 
 hipError_t launch_row_fused(const RowsumArgs& r, const NormArgs& a, int kind, hipStream_t st) {

@@ -86,3 +86,38 @@ def test_softmax_special_rows(dg, cols):
     torch.cuda.synchronize()
     assert_bits_equal(host_bits(Y), oracle.softmax(desc, X), "cols %d" % cols)
     assert torch.isnan(Y[1:4]).all() and not torch.isnan(Y[0]).any() and not torch.isnan(Y[4]).any()
+
+
+# both sides of each line at which row_fused_ok hands a call to the one-wave
+# kernels: (operation, leaf order, rows, cols)
+LINES = [("rmsnorm", 0, 256, 640), ("rmsnorm", 0, 257, 640), ("rmsnorm", 0, 2049, 640), ("rmsnorm", 0, 4, 2052),
+         ("rmsnorm", 0, 5, 2052), ("rmsnorm", 0, 513, 2052), ("rmsnorm", 1, 2048, 65), ("rmsnorm", 2, 2049, 65),
+         ("rmsnorm", 2, 4097, 513), ("layernorm", 1, 4096, 129), ("layernorm", 2, 4097, 129), ("softmax", 2, 2048, 129),
+         ("softmax", 1, 2049, 129), ("rmsnorm", 3, 1, 16384), ("rmsnorm", 3, 2, 16384), ("rmsnorm", 3, 9, 8196),
+         ("rmsnorm", 2, 3, 8196), ("rmsnorm", 2, 4, 8196), ("rmsnorm", 3, 257, 20000), ("rmsnorm", 2, 256, 20000),
+         ("rmsnorm", 2, 257, 20000), ("rmsnorm", 3, 33, 65540), ("rmsnorm", 1, 257, 65540), ("rowsum", 3, 1, 20000),
+         ("rowsum", 1, 2, 20000), ("rowsum", 1, 257, 16385), ("rowsum", 2, 513, 16388), ("layernorm", 3, 769, 16388)]
+
+
+@pytest.mark.parametrize("op,oi,rows,cols", LINES)
+def test_lines_between_row_kernels(dg, op, oi, rows, cols):
+    import torch
+    desc = dict(ORDERS[oi], out="f32", reduce="sumsq" if op == "rmsnorm" else "sum")
+    X = inputs.lognormal_f32(rows + cols, (rows, cols), sigma=1.0)
+    print("%s %s rows %d cols %d" % (op, desc, rows, cols), flush=True)
+    d, dX = dg.Desc(**desc), dev_f32(X)
+    got = torch.full((rows,) if op == "rowsum" else X.shape, float("nan"), device="cuda")
+    if op == "rowsum":
+        dg.dg_rowsum(d, dX, got)
+        want = oracle.rowsum(desc, X)
+    elif op == "rmsnorm":
+        dg.dg_rmsnorm(d, dX, None, 1e-5, got)
+        want = oracle.rmsnorm(desc, X, None, eps=1e-5)
+    elif op == "layernorm":
+        dg.dg_layernorm(d, dX, None, None, 1e-5, got)
+        want = oracle.layernorm(desc, X, None, None, eps=1e-5)
+    else:
+        dg.dg_softmax(d, dX, got)
+        want = oracle.softmax(desc, X)
+    torch.cuda.synchronize()
+    assert_bits_equal(host_bits(got), want, "%s %s %d x %d" % (op, desc, rows, cols))
