@@ -142,17 +142,13 @@ bool capturing(hipStream_t st) {
   return c != hipStreamCaptureStatusNone;
 }
 
-// Tile shape for the tiled kernel: a speed choice only.
-// The library's choice of kernel and tiles for the chunk-grid kernels
-// (speed only; every choice gives the same bits).  Measured on MI355X at
-// N = K = 4096 and at the decode and MLP shapes: few rows stream B through
-// the deep-ring kernel (whole 128-byte B rows per workgroup once the grid
-// is wide enough); larger M goes to the ping-pong kernel with 256 x 256
-// blocks when they fill most of the chip (mixed with 256 x 192 blocks when
-// that makes the last round over the chip fuller), else with 128 x 128
-// blocks, and
-// to the transposing-read kernel (two workgroups per CU, XCD-contiguous
-// grouped order) when even those are too few.
+// The library's choice of kernel and tiles for the chunk-grid kernels (speed
+// only; every choice gives the same bits): auto_config.  Few rows stream B
+// through the few-row kernel's deep ring of registers, large products run on
+// the ping-pong kernel's 256 x 256 blocks (mixed with 256 x 192 blocks when
+// that makes the last round over the chip fuller), the rest on the ring of
+// direct-to-LDS slabs (dg_gemm_ring.h); what does not fit 31-bit offsets on
+// the few-row and transposing-read kernels.
 struct AutoConfig {
   int kern, tm, tn, order, occ, depth, slab_k;
 };
@@ -241,13 +237,25 @@ bool ring_f8_config(int64_t M, int64_t N, int S, int ncu, int* tm, int* tn) {
 }
 
 // The kernel of a product on a chunk grid.  fits: pp_fits, the offsets of the
-// kernels that load through buffer resources.
-AutoConfig auto_config(int64_t M, int64_t N, int S, int ncu, bool fits) {
+// kernels that load through buffer resources; odd: sizes or pointers off the
+// 8-element grid.  Times are with operands from HBM.
+AutoConfig auto_config(int64_t M, int64_t N, int64_t K, int S, int ncu, bool fits, bool odd) {
   auto tiles = [&](int64_t tm, int64_t tn) { return S * ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
+  const int64_t t64 = S * ((N + 63) / 64), kp = K / S;   // 64-column tiles of all parts; a part's k
   // few rows: 16-column blocks while they are one round of the chip (1 x 4096
   // x 4096 11.9 us; 64-column ring blocks 14.6), past it the ring (1 x 5120 x
-  // 4096 14.9 against 18.4, 1 x 14272 x 3328 15.9 against 54)
-  if (M <= 32 && 4 * S * ((N + 63) / 64) <= ncu) return {4, 16, M <= 16 ? 16 : 32, 0, 0, 2, 256};
+  // 4096 14.9 against 18.4, 1 x 14272 x 3328 15.9 against 54), but for a block
+  // more per XCD and part (1 x 4224 x 4096 15.7 against 19.4; with column
+  // tiles that do not split over the XCDs the ring: 1 x 4160 x 4096 14.6, 21)
+  if (M <= 32 && 4 * t64 <= ncu) return {4, 16, M <= 16 ? 16 : 32, 0, 0, 2, 256};
+  if (M <= 16 && !odd && N % 128 == 0 && S * (N / 16) <= ncu + 8 * S && kp >= 1024) return {4, 16, 16, 0, 0, 2, 256};
+  // 64-column blocks of the few-row kernel where the ring's two per CU take a
+  // second round of short parts: 1 x 131072 x 256 16.6 us (the ring 22), 1 x
+  // 8320 x 4096 in four parts 21.3 (25.7), 16 x 36864 x 512 13.4 (15.1); long
+  // parts hide it: 16 x 49152 x 4096 87 (84), 1 x 16384 x 16384 in eight parts 89
+  // (78).  More than 16 rows are two row blocks there: 32 x 24576 x 1024 19.6 (14.1)
+  if (M <= 16 && !odd && t64 > 2 * ncu && (kp < 1024 || (t64 <= 3 * ncu && (S > 1 || kp == 1024))))
+    return {4, 16, 64, 0, 0, 4, 64};
   if (!fits) {
     if (M <= 32) return {4, 16, 64, 0, 0, 4, 64};
     if (M <= 128) return {4, 32, 64, 0, 0, 2, 256};
@@ -256,10 +264,17 @@ AutoConfig auto_config(int64_t M, int64_t N, int S, int ncu, bool fits) {
   // 256 x 256 blocks, each XCD given a contiguous range of them (2-3 % over
   // row-major order at 4096 x 4096 x 4096 on MI355X), where they fill three
   // quarters of the chip: 4096 x 4096 x 4096 117 us (the ring 132), or where
-  // the ring's 128 x 128 blocks would take a third round: with cold operands
-  // 1001 x 10656 x 4096 94.9 us (the ring 123.6), 1300 x 6144 x 2048 48.6
-  // (63.1), 2300 x 4096 x 8192 172 (181), 2560 x 4607 x 4095 152 (164)
-  if (tiles(256, 256) >= 192 || tiles(128, 128) > 2 * ncu) return {5, 256, 256, 3, 0, 0, 0};
+  // the ring's 128 x 128 blocks would take a third round: 1001 x 10656 x 4096
+  // 94.9 us (the ring 123.6), 1300 x 6144 x 2048 48.6 (63.1), 2300 x 4096 x 8192
+  // 172 (181), 2560 x 4607 x 4095 152 (164).  Not for up to 64 rows, three
+  // quarters of a block that do not exist: 1 x 9216 x 4096 in eight parts 38.9
+  // us (the ring 26.2), 32 x 65536 x 4096 101 (98), 64 x 9217 x 1023 in eight 46
+  // (31), but for odd sizes whose blocks fill their rounds, on which the ring's
+  // smaller ones wait for more unaligned loads: 64 x 128257 x 4095 239 (256).
+  // (128 x 14336 x 4096 in four parts 52.6, the ring 56.5; 200 x 65536 x 4096 129, 173)
+  const int64_t t256 = tiles(256, 256), rounds = (t256 + ncu - 1) / ncu;
+  const bool rows = M > 64 || (odd && M > 32 && rounds > 1 && 10 * t256 >= 9 * rounds * ncu);
+  if (rows && (t256 >= 192 || tiles(128, 128) > 2 * ncu)) return {5, 256, 256, 3, 0, 0, 0};
   AutoConfig c = {RING, 0, 0, 3, 0, 0, 0};
   ring_config(M, N, S, ncu, false, true, &c.tm, &c.tn);
   return c;
@@ -600,7 +615,7 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
   }
   if (kern == 1 && (tm || tn)) return DG_ERR_UNSUPPORTED;
   if (kern == 0 && tiled_ok) {
-    AutoConfig c = auto_config(M, N, a.S, cu_count(), pp_fits(a));
+    AutoConfig c = auto_config(M, N, K, a.S, cu_count(), pp_fits(a), false);
     if (c.kern == 5) {
       const int64_t sp = mixed_split(M, N, a.S, cu_count());
       if (sp >= 0) {
@@ -639,7 +654,7 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
       if (odd) kern = p.fma == 1 ? RING_TILES : 12;
       if (kern == RING_TILES) ring_config(M, N, a.S, cu_count(), true, p.tile_combine == DG_SEQ || part_tiles <= 8, &tm, &tn);
     } else if (odd) {
-      const AutoConfig c = auto_config(M, N, a.S, cu_count(), pp_fits(a));
+      const AutoConfig c = auto_config(M, N, K, a.S, cu_count(), pp_fits(a), true);
       kern = c.kern;
       tm = c.tm;
       tn = c.tn;

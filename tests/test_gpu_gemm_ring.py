@@ -150,3 +150,29 @@ def test_third_round(dg, desc, size):
     dg.dg_gemm(d, A, B, bias, ref, knobs=dict(kernel=1))
     torch.cuda.synchronize()
     assert_bits_equal(host_bits(C), host_bits(ref), "%s %s" % (size, desc))
+
+
+# few rows over many columns, on both sides of each line between the ring, the
+# few-row kernel's 16- and 64-column blocks and the 256-row blocks
+FEW = [(1, 4224, 1024, 1), (16, 2176, 2048, 2), (17, 2176, 2048, 2), (1, 32768, 128, 1), (16, 33280, 128, 1), (17, 33280, 128, 1),
+       (3, 16640, 512, 2), (16, 49152, 72, 1), (64, 49152, 72, 1), (65, 49152, 72, 1), (64, 49153, 65, 1), (64, 128257, 33, 1),
+       (32, 128257, 33, 1)]
+
+
+@pytest.mark.parametrize("M,N,K,S", FEW)
+def test_few_rows(dg, M, N, K, S):
+    import torch
+    desc = dict(tile_k=32, split_k=S, split_combine="tree", out="bf16", epilogue="bias")
+    A, B = inputs.spread_bf16(N + M, (M, K)), inputs.spread_bf16(N, (K, N))
+    bias = inputs.normal_bf16(K, (N,), 1.0)
+    odd = (N % 8 or K % 8) != 0
+    a, b, z = device(A, torch.bfloat16, odd), device(B, torch.bfloat16, odd), device(bias, torch.bfloat16, odd)
+    print("M %d N %d K %d S %d" % (M, N, K, S), flush=True)
+    C = [torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    dg.dg_gemm(dg.Desc(**desc), a, b, z, C[0])
+    dg.dg_gemm(dg.Desc(**desc), a, b, z, C[1], knobs=dict(kernel=1))
+    torch.cuda.synchronize()
+    assert torch.equal(C[0].view(torch.int16), C[1].view(torch.int16))
+    cols = np.r_[0:64, N // 2:N // 2 + 64, N - 64:N]
+    assert_bits_equal(host_bits(C[0])[:, cols], oracle.gemm(desc, A, np.ascontiguousarray(B[:, cols]), bias[cols]),
+                      "columns of %s" % ((M, N, K, S),))
