@@ -256,6 +256,14 @@ AutoConfig auto_config(int64_t M, int64_t N, int64_t K, int S, int ncu, bool fit
   // (78).  More than 16 rows are two row blocks there: 32 x 24576 x 1024 19.6 (14.1)
   if (M <= 16 && !odd && t64 > 2 * ncu && (kp < 1024 || (t64 <= 3 * ncu && (S > 1 || kp == 1024))))
     return {4, 16, 64, 0, 0, 4, 64};
+  // 33 to 128 rows, long parts and B's rows a multiple of 1 KB apart: the few-row
+  // kernel's 32 x 64 blocks while they are one round and fill their 64 rows
+  // (64 x 6144 x 8192 46.1 us, the ring 52.6; 128 x 4096 x 8192 42.9, 48.2; 64 x
+  // 4096 x 4096 24.9, 26.8); else the ring (65 x 4096 x 8192 40.7, 37.6; 64 x
+  // 3008 x 8192 41.2, 40.4; 64 x 4096 x 1024 10.8, 9.8)
+  if (M > 32 && M <= 128 && !odd && (M + 31) / 32 % 2 == 0 && N % 512 == 0 && tiles(32, 64) <= ncu &&
+      (kp >= 8192 || (kp >= 4096 && N >= 4096)))
+    return {4, 32, 64, 0, 0, 2, 256};
   if (!fits) {
     if (M <= 32) return {4, 16, 64, 0, 0, 4, 64};
     if (M <= 128) return {4, 32, 64, 0, 0, 2, 256};

@@ -156,7 +156,7 @@ def test_third_round(dg, desc, size):
 # few-row kernel's 16- and 64-column blocks and the 256-row blocks
 FEW = [(1, 4224, 1024, 1), (16, 2176, 2048, 2), (17, 2176, 2048, 2), (1, 32768, 128, 1), (16, 33280, 128, 1), (17, 33280, 128, 1),
        (3, 16640, 512, 2), (16, 49152, 72, 1), (64, 49152, 72, 1), (65, 49152, 72, 1), (64, 49153, 65, 1), (64, 128257, 33, 1),
-       (32, 128257, 33, 1)]
+       (32, 128257, 33, 1), (33, 512, 8192, 1), (64, 512, 8184, 1), (65, 512, 8192, 1), (128, 4096, 4096, 1)]
 
 
 @pytest.mark.parametrize("M,N,K,S", FEW)
