@@ -646,10 +646,14 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
   // with chunks loaded where they lie (dg_gemm_odd.hip).  A short leading tile
   // must still be whole chunks, because the chunk grid restarts after it, and
   // the last chunk of each matrix must lie in its last row (N, K >= 8); the
-  // rest stays on the generic kernel.
+  // rest stays on the generic kernel, and so do parts of one slab (a lone tile
+  // chain's or tree's, a little more) while its waves, one per 16 x 16 outputs,
+  // are at most four a CU: 25 x 333 x 20 4.3 us, the ring 6.7; 64 x 3001 x 45 5.2,
+  // 5.8 (91 x 3001 x 45: 8.1, 5.7); 40 x 333 x 71 5.8, 5.6, as a tree 6.5, 6.9; 25 x
+  // 97 x 206 in four parts 7.9, 10.2.
   bool odd = false;
   if (kern == 0 && !f8 && !strided && N >= 8 && K >= 8) {
-    odd = true;
+    odd = K > (gen && a.S == 1 ? 80 : 64 * (int64_t)a.S) || a.S * ((M + 15) / 16) * ((N + 15) / 16) > 4 * (int64_t)cu_count();
     for (int s = 0; s < a.S; ++s) {
       const int64_t len = a.cuts[s + 1] - a.cuts[s];
       if (a.tail_first && (len % p.tile_k) % (gen ? 32 : 8)) odd = false;

@@ -92,3 +92,32 @@ def test_odd_sizes_wide(dg, shape):
     rows = np.array([0, 1, M // 2, M - 2, M - 1])
     assert_bits_equal(host_bits(C)[rows], oracle.gemm(desc, A[rows], B, bias), "rows of %s" % (shape,))
     assert_bits_equal(host_bits(s), oracle.colsum(host_bits(C)), "column sums of %s" % (shape,))
+
+
+# parts of one slab: both sides of the line between the generic kernel and the
+# tiled ones, and every block shape of the latter with a single slab
+SHORT = [(25, 333, 20), (40, 333, 71), (64, 2999, 45), (91, 3001, 45), (500, 1021, 9), (500, 1021, 61), (700, 2999, 63),
+         (1500, 3001, 64)]
+
+
+@pytest.mark.parametrize("shape", SHORT)
+@pytest.mark.parametrize("di", range(5))
+def test_odd_short_parts(dg, di, shape):
+    import torch
+    desc = [dict(tile_k=32, out="bf16", epilogue="bias"), dict(tile_k=32, tile_combine="tree"),
+            dict(tile_k=64, tile_combine="seq", in_dtype="f16"), dict(tile_k=32, fma=0),
+            dict(tile_k=32, split_k=2, split_combine="tree")][di]
+    M, N, K = shape
+    if desc.get("split_k") and K <= 32:
+        K += 32
+    f16 = desc.get("in_dtype") == "f16"
+    dt = torch.float16 if f16 else torch.bfloat16
+    spread = inputs.spread_f16 if f16 else inputs.spread_bf16
+    A, B = spread(di + M, (M, K)), spread(di + N, (K, N))
+    bias = inputs.normal_bf16(M + 2, (N,), 1.0) if "epilogue" in desc else None
+    print("shape %s desc %s" % ((M, N, K), desc), flush=True)
+    C = torch.full((M, N), float("nan"), dtype=torch.bfloat16 if desc.get("out") == "bf16" else torch.float32, device="cuda")
+    dg.dg_gemm(dg.Desc(**desc), inside(A, dt), inside(B, dt), None if bias is None else inside(bias, torch.bfloat16), C)
+    torch.cuda.synchronize()
+    rows = np.unique(np.r_[0:min(M, 70), M // 2, M - 66 if M > 66 else 0:M])
+    assert_bits_equal(host_bits(C)[rows], oracle.gemm(desc, np.ascontiguousarray(A[rows]), B, bias), "%s %s" % (shape, desc))
