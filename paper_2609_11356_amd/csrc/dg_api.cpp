@@ -593,8 +593,20 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
   }
   int tc_levels = 2;
   while (tc_levels < 7 && part_tiles > ((int64_t)1 << tc_levels)) ++tc_levels;
-  // the ring's tree (fma = 1): at most 256 tiles per part
-  const bool ring_tiles = tc_ok && p.fma == 1 && (p.tile_combine != DG_TREE || part_tiles <= 256) && pp_fits(a);
+  // the ring's tree (fma = 1): at most 256 tiles per part.  Nine to sixteen
+  // stay on the tile-combine kernel, whose stack of four levels leaves it two
+  // 128 x 64 blocks per CU, where the ring's one 64 x 128 block (eight levels)
+  // takes so many more rounds: one of its rounds takes 1.6 of the ring's with
+  // tiles of 32 (2048 x 8192 x 512 60.1 us, the ring 74.3; 617 x 8192 x 512 28.4,
+  // 27.5), nearly two with longer ones, which leaves it a ring's second round of
+  // few blocks (tile_k 256: 400 x 5696 x 4096, 315 of them, 65.6 and 76.1; 1500 x
+  // 2048 x 4096, 384, 67.2 and 60.9; 1000 x 5696 x 4096, 720, 121 and 103).
+  bool ring_tiles = tc_ok && p.fma == 1 && (p.tile_combine != DG_TREE || part_tiles <= 256) && pp_fits(a);
+  if (ring_tiles && p.tile_combine == DG_TREE && part_tiles > 8 && part_tiles <= 16) {
+    const int64_t ncu = cu_count(), ring_blocks = a.S * ((M + 63) / 64) * ((N + 127) / 128);
+    const int64_t rr = (ring_blocks + ncu - 1) / ncu, rt = (a.S * ((M + 127) / 128) * ((N + 63) / 64) + 2 * ncu - 1) / (2 * ncu);
+    if (p.tile_k <= 32 ? 5 * rr > 8 * rt : rr == 2 && rt == 1 && 20 * ring_blocks <= 27 * ncu) ring_tiles = false;
+  }
   if (p.tile_combine == DG_TREE && part_tiles > 128) tc_ok = false;
   if (scalar) {
     tiled_ok = false;

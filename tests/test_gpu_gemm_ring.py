@@ -176,3 +176,26 @@ def test_few_rows(dg, M, N, K, S):
     cols = np.r_[0:64, N // 2:N // 2 + 64, N - 64:N]
     assert_bits_equal(host_bits(C[0])[:, cols], oracle.gemm(desc, A, np.ascontiguousarray(B[:, cols]), bias[cols]),
                       "columns of %s" % ((M, N, K, S),))
+
+
+# trees of nine to sixteen tiles, on both sides of the line between the ring and
+# the tile-combine kernel (rounds of the chip that each would take)
+TREES = [(400, 5696, 512, 32), (1000, 5696, 512, 32), (64, 5696, 512, 32), (2048, 2056, 288, 32), (400, 5696, 576, 64),
+         (1000, 5696, 1024, 64), (400, 5696, 2304, 256)]
+
+
+@pytest.mark.parametrize("M,N,K,tile_k", TREES)
+def test_tree_of_nine_to_sixteen(dg, M, N, K, tile_k):
+    import torch
+    desc = dict(tile_k=tile_k, tile_combine="tree", out="bf16", epilogue="bias")
+    A, B = inputs.spread_bf16(N + M, (M, K)), inputs.spread_bf16(N, (K, N))
+    bias = inputs.normal_bf16(K, (N,), 1.0)
+    a, b, z = device(A, torch.bfloat16, 0), device(B, torch.bfloat16, 0), device(bias, torch.bfloat16, 0)
+    print("M %d N %d K %d tile_k %d" % (M, N, K, tile_k), flush=True)
+    C = [torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    dg.dg_gemm(dg.Desc(**desc), a, b, z, C[0])
+    dg.dg_gemm(dg.Desc(**desc), a, b, z, C[1], knobs=dict(kernel=1))
+    torch.cuda.synchronize()
+    assert torch.equal(C[0].view(torch.int16), C[1].view(torch.int16))
+    rows = np.array([0, M // 2, M - 1])
+    assert_bits_equal(host_bits(C[0])[rows], oracle.gemm(desc, A[rows], B, bias), "rows of %s" % ((M, N, K, tile_k),))
