@@ -63,3 +63,25 @@ def test_parts_and_addresses(dg, kind, S, off):
         bias = inputs.normal_bf16(n, (N,)) if "epilogue" in desc else None
         print("packed", desc, (M, N, K), off, flush=True)
         assert_bits_equal(run(dg, desc, A, B, bias, off), oracle.gemm(desc, A, B, bias), "%s %s" % (desc, (M, N, K)))
+
+
+@pytest.mark.parametrize("kind", ["bf16", "bf16_e4m3"])
+@pytest.mark.parametrize("shape", [(48, 4112, 512, 2), (48, 4112, 4096, 2), (64, 1024, 512, 4), (64, 1024, 2048, 4),
+                                   (16, 512, 8192, 8), (16, 512, 2048, 8), (9, 8192, 1024, 3), (17, 5760, 6144, 8)])
+def test_merged_and_apart(dg, kind, shape):
+    """Both sides of the line between parts that meet in the kernel and parts
+    that a second launch merges, against the row-major product."""
+    import torch
+    M, N, K, S = shape
+    desc = dict(tile_k=64, split_k=S, split_combine="tree", in_dtype=kind, out="bf16", epilogue="bias")
+    rng = np.random.default_rng(K)
+    A = inputs.spread_bf16(M, (M, K))
+    B = rng.integers(0, 256, (K, N), dtype=np.uint8) & 0xF7 if kind == "bf16_e4m3" else inputs.spread_bf16(N, (K, N))
+    bias = inputs.normal_bf16(N, (N,))
+    print("packed", desc, shape, flush=True)
+    got = run(dg, desc, A, B, bias, 0)
+    dB = torch.from_numpy(np.ascontiguousarray(B)).cuda() if kind == "bf16_e4m3" else dev_bf16(B)
+    C = torch.full((M, N), 7.0, device="cuda", dtype=torch.bfloat16)
+    dg.dg_gemm(dg.Desc(**desc), dev_bf16(A), dB, dev_bf16(bias), C)
+    torch.cuda.synchronize()
+    assert_bits_equal(got, host_bits(C), "%s %s" % (desc, shape))
