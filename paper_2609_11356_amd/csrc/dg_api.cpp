@@ -509,13 +509,11 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
         if (a.cuts[s] % run_k) return DG_ERR_UNSUPPORTED;
     }
     if (!aligned(B, 16)) return DG_ERR_ALIGN;
-    // every buffer offset (the packed B, A's rows) stays in 31 bits
+    // the buffer offsets (the packed B, A's rows) stay in 31 bits, A's from up to 14 bytes before its start
     if ((b8 ? dg_packed_b8_bytes(K, N) : dg_packed_b_bytes(K, N)) > 0x7fffffff || M * K * 2 > 0x7fffffff)
       return DG_ERR_UNSUPPORTED;
     panel_tms = tm ? tm / 16 : (M <= 16 ? 1 : M <= 32 ? 2 : 4);
     panel_avec = K % 8 == 0 && aligned(A, 16);
-    // offsets from 16 bytes before A's start: 16-row blocks where 64 rows would pass 31 bits
-    if (!panel_avec && !tm && M * K * 2 > 0x7fffffff - 16) panel_tms = 1;
     panel_depth = depth ? depth : dg::panel_default_depth(panel_tms, b8);
     if (panel_avec || !depth) {
       if (!dg::panel_supported(panel_tms, panel_depth, b8)) return DG_ERR_UNSUPPORTED;

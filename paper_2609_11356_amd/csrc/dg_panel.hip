@@ -44,7 +44,9 @@ namespace dg {
 
 namespace {
 
-constexpr uint32_t kOOB = 0x80000000u;   // a buffer offset past any record: reads zero
+// A buffer offset past any record, so that it reads zero: A's bytes (below 2^31,
+// the host checks) with up to 14 before its start, B's below 2^31.
+constexpr uint32_t kOOB = 0x80000010u;
 
 // 8 values of one A row from k on, each checked against K (the block that K
 // cuts short, where A's rows do not lie on 16 bytes); mis: the bytes between
@@ -86,8 +88,8 @@ __global__ __launch_bounds__(FUSE ? 512 : 64) void gemm_panel(GemmArgs a) {
   const int64_t panel = blockIdx.x;
   const int64_t i0 = (int64_t)blockIdx.y * 16 * TMS, j0 = panel * 16;
   const int s = FUSE ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : blockIdx.z;
-  // every k block index and byte offset fits 31 bits (the host keeps the
-  // packed B under 2 GiB and A's rows under 2 GiB)
+  // every k block index fits 31 bits, every byte offset 32 (the host keeps the
+  // packed B and A under 2 GiB)
   const int KR = (int)((a.K + 32 * BPR - 1) / (32 * BPR)), K = (int)a.K;
   // blocks (nf) and runs (nr) of part s: contiguous from run r0 (the host
   // puts interior cuts on run boundaries), or dealt tiles of 2^lgw blocks
@@ -107,7 +109,7 @@ __global__ __launch_bounds__(FUSE ? 512 : 64) void gemm_panel(GemmArgs a) {
   const uint32_t misA = AVEC ? 0 : (uint32_t)((uintptr_t)(a.A + i0 * a.K) & 15);
   const int64_t recA = (a.M - i0) * a.K * 2 + misA, recB = ((a.N + 15) / 16) * (int64_t)KR * RUN;
   const __amdgpu_buffer_rsrc_t rA = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)((const char*)(a.A + i0 * a.K) - misA), (short)0, (int)(recA < 0x7fffffff ? recA : 0x7fffffff), 0x00020000);
+      (void*)((const char*)(a.A + i0 * a.K) - misA), (short)0, (int)(uint32_t)recA, 0x00020000);
   // the panel's runs: a base moved to the panel, the run in the scalar offset
   const __amdgpu_buffer_rsrc_t rB = __builtin_amdgcn_make_buffer_rsrc((void*)a.B, (short)0, (int)recB, 0x00020000);
   const int kl = 8 * (lane >> 4);   // the lane's first k within a block

@@ -85,3 +85,31 @@ def test_merged_and_apart(dg, kind, shape):
     dg.dg_gemm(dg.Desc(**desc), dev_bf16(A), dB, dev_bf16(bias), C)
     torch.cuda.synchronize()
     assert_bits_equal(got, host_bits(C), "%s %s" % (desc, shape))
+
+
+@pytest.mark.parametrize("M,K,off", [(9, 119304647, 7), (11, 97612893, 7), (9, 119304647, 1)])
+def test_a_at_two_gib(dg, M, K, off):
+    """A of 2 GiB less a few bytes, off 16 bytes: the offsets of its last
+    elements pass 2^31.  Zeros but for the first and last k, small integers
+    there, so that every sum is exact whatever its order."""
+    import torch
+    N, S, n = 16, 64, 48
+    desc = dict(tile_k=64, split_k=S, split_combine="tree", in_dtype="bf16_e4m3", out="f32")
+    rng = np.random.default_rng(M + off)
+    head, tail = (rng.integers(-3, 4, (M, n)).astype(np.float32) for _ in range(2))
+    bh, bt = (rng.integers(-3, 4, (n, N)).astype(np.float32) for _ in range(2))
+    print("M %d K %d off %d" % (M, K, off), flush=True)
+    buf = torch.zeros(M * K + off + 9, dtype=torch.bfloat16, device="cuda")
+    buf[:off] = float("nan")
+    buf[off + M * K:] = float("nan")
+    A = buf[off:off + M * K].view(M, K)
+    assert A.data_ptr() % 16 == 2 * off
+    A[:, :n], A[:, K - n:] = torch.from_numpy(head).cuda(), torch.from_numpy(tail).cuda()
+    B = torch.zeros((K, N), dtype=torch.float8_e4m3fn, device="cuda")
+    B[:n], B[K - n:] = (torch.from_numpy(x).cuda().to(torch.float8_e4m3fn) for x in (bh, bt))
+    Bp = dg.dg_pack_b(B)
+    del B
+    C = torch.full((M, N), 7.0, device="cuda")
+    dg.dg_gemm_packed(dg.Desc(**desc), A, Bp, None, C)
+    torch.cuda.synchronize()
+    assert np.array_equal(C.cpu().numpy(), head @ bh + tail @ bt)
