@@ -271,8 +271,9 @@ dg_status dg_pack_b(const void* B, void* Bp, int64_t K, int64_t N, void* stream)
  * multiples of 32 (64 for an e4m3 B), or strided parts dealing tiles of
  * 32 * 2^j k (64 * 2^j for an e4m3 B).
  * DG_ERR_UNSUPPORTED for anything else (M > 64 included), DG_ERR_ALIGN if Bp
- * is not 16-byte aligned; errors otherwise as dg_gemm, and split-K uses the
- * same workspace. */
+ * is not 16-byte aligned; errors otherwise as dg_gemm.  Split-K uses the
+ * same workspace, or none where two to eight contiguous parts meet in the
+ * kernel (one launch). */
 dg_status dg_gemm_packed(const dg_desc* d, const void* A, const void* Bp, const void* bias,
                          void* C, int64_t M, int64_t N, int64_t K, void* stream);
 

@@ -550,8 +550,10 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
     }
   }
   hipStream_t st = (hipStream_t)stream;
+  // the packed kernel merges the parts itself: no partials, no workspace
+  const bool panel_merge = kern == 11 && dg::panel_merges(a, panel_tms, panel_depth, cu_count());
   Lease lease;
-  if (a.S > 1) {
+  if (a.S > 1 && !panel_merge) {
     void* ws = nullptr;
     const size_t bytes = (size_t)a.S * (size_t)M * (size_t)N * sizeof(float);
     if (noalloc) {
@@ -688,7 +690,6 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
     a.colsum_part = colsum_part;
     *fused = true;
   }
-  bool panel_merge = false;   // the packed kernel merges the parts itself
   hipError_t e;
   if (kern == RING) {
     a.order = order;
@@ -703,7 +704,6 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
     a.order = kern == 12 ? 1 : order;
     e = kern == 12 ? dg::launch_gemm_odd_tc(a, st) : dg::launch_gemm_odd(a, kern, tm, tn, st);
   } else if (kern == 11) {
-    panel_merge = dg::panel_merges(a, panel_tms, panel_depth, cu_count());
     e = dg::launch_gemm_panel(a, panel_tms, panel_depth, panel_avec, panel_merge, st);
   } else if (kern == 14) {
     if (((M + 255) / 256) * ((N + 127) / 128) > INT32_MAX) return DG_ERR_SHAPE;

@@ -113,3 +113,25 @@ def test_a_at_two_gib(dg, M, K, off):
     dg.dg_gemm_packed(dg.Desc(**desc), A, Bp, None, C)
     torch.cuda.synchronize()
     assert np.array_equal(C.cpu().numpy(), head @ bh + tail @ bt)
+
+
+def test_merged_takes_no_workspace(dg):
+    """Parts that meet in the kernel leave no partials: on a stream of its own,
+    whose workspace would have to grow by S M N 4 bytes, no device memory goes."""
+    import ctypes
+
+    import torch
+    M, N, K, S = 64, 65536, 512, 8
+    A = torch.ones((M, K), dtype=torch.bfloat16, device="cuda")
+    Bp = dg.dg_pack_b(torch.ones((K, N), dtype=torch.bfloat16, device="cuda"))
+    C = torch.zeros((M, N), dtype=torch.bfloat16, device="cuda")
+    hip = ctypes.CDLL("libamdhip64.so")
+    stream = ctypes.c_void_p()
+    torch.cuda.synchronize()
+    assert hip.hipStreamCreate(ctypes.byref(stream)) == 0
+    free = torch.cuda.mem_get_info()[0]
+    dg.dg_gemm_packed(dg.Desc(tile_k=64, split_k=S, split_combine="tree", out="bf16"), A, Bp, None, C, stream=stream.value)
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] < S * M * N * 4 // 2
+    assert hip.hipStreamDestroy(stream) == 0
+    assert (C == K).all()
