@@ -519,9 +519,9 @@ void dg_attn_desc_destroy(dg_attn_desc* d);
  * H = 0 or Lq = 0 is a no-op.  DG_ERR_SHAPE for Lk < 1, H > 65535,
  * Lq > 16 * 65535, or a causal descriptor with Lq != Lk; DG_ERR_UNSUPPORTED for another d;
  * DG_ERR_ALIGN for a pointer not 16-byte aligned.  One launch on stream; for
- * few query rows over many keys three launches through the library-owned
- * workspace of the (device, stream) (never while the stream is captured, and
- * one launch again if the workspace cannot grow). */
+ * few query rows over many keys three launches through a library-owned
+ * workspace of the (device, stream), attention's own (at most 320 MB; never
+ * while the stream is captured, and one launch again if it cannot grow). */
 dg_status dg_attention(const dg_attn_desc* d, const void* Q, const void* K, const void* V, void* O,
                        int64_t H, int64_t Lq, int64_t Lk, int64_t dim, float qk_scale, void* stream);
 

@@ -9,6 +9,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <tuple>
 #include <utility>
 
 #include "dg_internal.h"
@@ -95,8 +96,12 @@ struct Workspace {
   size_t bytes = 0;
   std::recursive_mutex mu;   // held by the call whose launches use ptr
 };
+// Attention has a workspace of its own: a captured call of the others may hold
+// theirs, and attention, which is never captured with one, must not be what
+// makes it grow and frees it under the graph.
+enum WsUse { WS_SUMS = 0, WS_ATTENTION = 1 };
 std::mutex g_ws_mutex;       // the map
-std::map<std::pair<int, hipStream_t>, Workspace> g_ws;
+std::map<std::tuple<int, hipStream_t, int>, Workspace> g_ws;
 
 // A call's hold on its workspace: until the lease ends (the call has enqueued
 // all of its launches) no other host thread gets the same stream's workspace,
@@ -106,13 +111,13 @@ typedef std::unique_lock<std::recursive_mutex> Lease;
 // Workspace of at least `bytes` owned by (current device, stream).  Growth is
 // stream-ordered (hipMallocAsync / hipFreeAsync on that stream), so launches
 // already enqueued on the stream keep their buffer until they finish.
-dg_status get_workspace(hipStream_t st, size_t bytes, void** out, Lease* lease) {
+dg_status get_workspace(hipStream_t st, size_t bytes, void** out, Lease* lease, WsUse use = WS_SUMS) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return DG_ERR_HIP;
   Workspace* w;
   {
     std::lock_guard<std::mutex> lock(g_ws_mutex);
-    w = &g_ws[{dev, st}];    // a map node never moves
+    w = &g_ws[{dev, st, use}];    // a map node never moves
   }
   *lease = Lease(w->mu);
   if (w->bytes < bytes) {
@@ -1173,7 +1178,7 @@ dg_status dg_attention(const dg_attn_desc* d, const void* Q, const void* K, cons
     // the blocks over the chip; without memory for the records, one launch
     void* ws = nullptr;
     Lease lease;
-    if (get_workspace(st, dg::attn_split_bytes(a, d->p.key_block), &ws, &lease) == DG_OK) {
+    if (get_workspace(st, dg::attn_split_bytes(a, d->p.key_block), &ws, &lease, WS_ATTENTION) == DG_OK) {
       if (dg::launch_attention_split(a, dim, d->p.key_block, (float*)ws, st) != hipSuccess) return DG_ERR_HIP;
       return DG_OK;
     }

@@ -128,3 +128,34 @@ def test_few_rows_under_capture(dg):
         assert torch.equal(got.view(torch.int16), want.view(torch.int16))
         dg.dg_attention(desc, Q, K, V, want, scale(128))
         torch.cuda.synchronize()
+
+
+def test_attention_leaves_a_captured_workspace(dg):
+    """Attention on a stream does not touch the workspace that a captured
+    split-K product of the same stream holds: the graph replays to the eager
+    bits after an attention call that needs far more."""
+    import torch
+    from tests.gpu_util import dev_bf16
+    stream = torch.cuda.Stream()
+    A, B = dev_bf16(inputs.normal_bf16(1, (16, 512))), dev_bf16(inputs.normal_bf16(2, (512, 256)))
+    Q, K, V = (dev_bf16(x) for x in qkv(5, 16, 4, 2048, 128))
+    O = torch.empty(Q.shape, dtype=torch.bfloat16, device="cuda")
+    gemm, attn = dg.Desc(tile_k=64, split_k=4, split_combine="tree"), dg.AttnDesc(key_block=64)
+    want, got = torch.empty((16, 256), device="cuda"), torch.empty((16, 256), device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        dg.dg_gemm(gemm, A, B, None, want)       # the workspace is there before the capture
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        dg.dg_gemm(gemm, A, B, None, got)
+    for n in range(3):
+        with torch.cuda.stream(stream):
+            dg.dg_attention(attn, Q, K, V, O, scale(128))
+        torch.cuda.synchronize()
+        keep = torch.full((1 << 20,), 3.0, device="cuda")    # memory that the replay must not write
+        got.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got, want) and (keep == 3.0).all()
