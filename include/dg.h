@@ -28,6 +28,13 @@
  *     nothing was launched and no output was written.
  *   - A descriptor is immutable after dg_desc_create and may be used from any
  *     number of host threads and streams at once.
+ *   - Library-owned workspaces are kept per (device, stream handle), grow in
+ *     stream order and stay until the process ends.  Under hipStreamPerThread,
+ *     one handle for a stream of every host thread, a call allocates and frees
+ *     its own in stream order instead.  A stream may be destroyed only when its
+ *     work is done, as a later stream can get the same handle.  A captured call
+ *     keeps the workspace it found; the graph must not be replayed after a call
+ *     on that stream that needs a larger one (dg_gemm_noalloc never does).
  */
 #ifndef DG_H
 #define DG_H

@@ -103,23 +103,58 @@ enum WsUse { WS_SUMS = 0, WS_ATTENTION = 1 };
 std::mutex g_ws_mutex;       // the map
 std::map<std::tuple<int, hipStream_t, int>, Workspace> g_ws;
 
+bool capturing(hipStream_t st);
+
 // A call's hold on its workspace: until the lease ends (the call has enqueued
 // all of its launches) no other host thread gets the same stream's workspace,
 // so the launches of two calls on one stream cannot interleave over it.
-typedef std::unique_lock<std::recursive_mutex> Lease;
+class Lease {
+ public:
+  Lease() = default;
+  Lease(const Lease&) = delete;
+  Lease& operator=(const Lease&) = delete;
+  ~Lease() { release(); }
+  void lock(std::recursive_mutex& mu) { hold = std::unique_lock<std::recursive_mutex>(mu); }
+  void own(void* p, hipStream_t st) {   // a buffer of this call's alone
+    release();
+    ptr = p;
+    stream = st;
+  }
+
+ private:
+  void release() {
+    if (ptr) (void)hipFreeAsync(ptr, stream);
+    ptr = nullptr;
+  }
+  std::unique_lock<std::recursive_mutex> hold;
+  void* ptr = nullptr;
+  hipStream_t stream = nullptr;
+};
 
 // Workspace of at least `bytes` owned by (current device, stream).  Growth is
 // stream-ordered (hipMallocAsync / hipFreeAsync on that stream), so launches
 // already enqueued on the stream keep their buffer until they finish.
+// hipStreamPerThread is one handle for a stream of every host thread, so
+// nothing is kept under it: the call gets a buffer of its own, freed in
+// stream order when the lease ends (under capture, where that would put
+// allocations into the graph, the kept one, as on any stream).
 dg_status get_workspace(hipStream_t st, size_t bytes, void** out, Lease* lease, WsUse use = WS_SUMS) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return DG_ERR_HIP;
+  if (st == hipStreamPerThread && !capturing(st)) {
+    if (hipMallocAsync(out, bytes, st) != hipSuccess) {
+      (void)hipGetLastError();
+      return DG_ERR_NOMEM;
+    }
+    lease->own(*out, st);
+    return DG_OK;
+  }
   Workspace* w;
   {
     std::lock_guard<std::mutex> lock(g_ws_mutex);
     w = &g_ws[{dev, st, use}];    // a map node never moves
   }
-  *lease = Lease(w->mu);
+  lease->lock(w->mu);
   if (w->bytes < bytes) {
     size_t want = bytes + bytes / 4;
     void* p = nullptr;

@@ -159,3 +159,47 @@ def test_attention_leaves_a_captured_workspace(dg):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(got, want) and (keep == 3.0).all()
+
+
+def test_two_threads_on_the_per_thread_stream(dg):
+    """hipStreamPerThread is one handle for two queues: calls of two host
+    threads on it share no workspace (attention's records, split-K partials)."""
+    import threading
+
+    import torch
+    from tests.gpu_util import dev_bf16
+    PER_THREAD = 2                       # hipStreamPerThread
+    attn, gemm = dg.AttnDesc(key_block=64), dg.Desc(tile_k=64, split_k=4, split_combine="tree")
+    work = []
+    for t in range(2):
+        Q, K, V = (dev_bf16(x) for x in qkv(40 + t, 4, 1, 3001, 128))
+        A, B = dev_bf16(inputs.normal_bf16(50 + t, (8, 1024))), dev_bf16(inputs.normal_bf16(60 + t, (1024, 512)))
+        wants = torch.empty(Q.shape, dtype=torch.bfloat16, device="cuda"), torch.empty((8, 512), device="cuda")
+        dg.dg_attention(attn, Q, K, V, wants[0], scale(128))
+        dg.dg_gemm(gemm, A, B, None, wants[1])
+        outs = [(torch.zeros_like(wants[0]), torch.zeros_like(wants[1])) for _ in range(100)]
+        work.append((Q, K, V, A, B, wants, outs))
+    torch.cuda.synchronize()
+    start, failed = threading.Barrier(2), []
+
+    def body(w):
+        Q, K, V, A, B, _, outs = w
+        try:
+            start.wait(timeout=60)
+            for o, c in outs:
+                dg.dg_attention(attn, Q, K, V, o, scale(128), stream=PER_THREAD)
+                dg.dg_gemm(gemm, A, B, None, c, stream=PER_THREAD)
+            torch.cuda.synchronize()
+        except BaseException as e:
+            failed.append(e)
+
+    threads = [threading.Thread(target=body, args=(w,)) for w in work]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(timeout=100)
+    assert not failed and not any(t.is_alive() for t in threads), failed
+    torch.cuda.synchronize()
+    for _, _, _, _, _, wants, outs in work:
+        for o, c in outs:
+            assert torch.equal(o.view(torch.int16), wants[0].view(torch.int16)) and torch.equal(c, wants[1])
