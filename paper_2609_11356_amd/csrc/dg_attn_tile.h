@@ -1,7 +1,6 @@
 // dg_attn_tile.h -- device pieces shared by the attention kernels: operand
-// types, the MFMA wrappers, lane-group exchanges, the base-two exponential of
-// non-positive values, and the key order and LDS swizzles of transposed score
-// tiles.
+// types, the MFMA wrappers, lane-group exchanges, and the key order and LDS
+// swizzles of transposed score tiles.
 #pragma once
 
 #include <type_traits>
@@ -65,25 +64,6 @@ __device__ __forceinline__ void rows_swap(float& a, float& b) {
   const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(int, a), __builtin_bit_cast(int, b), false, false);
   a = __builtin_bit_cast(float, (int)r[0]);
   b = __builtin_bit_cast(float, (int)r[1]);
-}
-
-// exp2_f32 for x <= 0, -inf or NaN (every score minus the running maximum):
-// the same steps and bits.  Only the lower clamp can be reached; as
-// v_maximum3 it lets a NaN through, which then passes every later step.
-__device__ __forceinline__ float exp2_nonpos(float x_in) {
-  float x;
-  asm("v_maximum3_f32 %0, %1, %2, %2" : "=v"(x) : "v"(x_in), "s"(-151.0f));
-  const float n = __builtin_rintf(x);
-  const float f = x - n;
-  float p = 0x1.ffcbfcp-17f;
-  p = __builtin_fmaf(p, f, 0x1.430912p-13f);
-  p = __builtin_fmaf(p, f, 0x1.5d87fep-10f);
-  p = __builtin_fmaf(p, f, 0x1.3b2ab6p-7f);
-  p = __builtin_fmaf(p, f, 0x1.c6b08ep-5f);
-  p = __builtin_fmaf(p, f, 0x1.ebfbep-3f);
-  p = __builtin_fmaf(p, f, 0x1.62e43p-1f);
-  p = __builtin_fmaf(p, f, 1.0f);
-  return __builtin_ldexpf(p, (int)n);
 }
 
 // Key of MFMA row r of a K tile, and the swizzle of the K and V rows in LDS

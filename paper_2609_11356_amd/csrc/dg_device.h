@@ -96,6 +96,44 @@ __device__ __forceinline__ float exp2_f32(float x_in) {
   return x_in != x_in ? x_in + x_in : e;
 }
 
+// exp_f32 for x <= 0 or NaN (softmax's x_j - max): the same steps and bits; the
+// upper clamp is never reached, and the lower one as a select lets a NaN
+// through the polynomial by itself.
+__device__ __forceinline__ float exp_nonpos(float x_in) {
+  const float x = x_in < -104.0f ? -104.0f : x_in;
+  const float n = __builtin_rintf(x * 0x1.715476p+0f);
+  float r = __builtin_fmaf(-n, 0x1.62e4p-1f, x);
+  r = __builtin_fmaf(-n, 0x1.7f7d1cp-20f, r);
+  float p = 0x1.a01a02p-13f;
+  p = __builtin_fmaf(p, r, 0x1.6c16c2p-10f);
+  p = __builtin_fmaf(p, r, 0x1.111112p-7f);
+  p = __builtin_fmaf(p, r, 0x1.555556p-5f);
+  p = __builtin_fmaf(p, r, 0x1.555556p-3f);
+  p = __builtin_fmaf(p, r, 0.5f);
+  p = __builtin_fmaf(p, r, 1.0f);
+  p = __builtin_fmaf(p, r, 1.0f);
+  return __builtin_ldexpf(p, (int)n);
+}
+
+// exp2_f32 for x <= 0, -inf or NaN (attention's score minus the running
+// maximum): the same steps and bits.  Only the lower clamp can be reached; as
+// v_maximum3 it lets a NaN through, which then passes every later step.
+__device__ __forceinline__ float exp2_nonpos(float x_in) {
+  float x;
+  asm("v_maximum3_f32 %0, %1, %2, %2" : "=v"(x) : "v"(x_in), "s"(-151.0f));
+  const float n = __builtin_rintf(x);
+  const float f = x - n;
+  float p = 0x1.ffcbfcp-17f;
+  p = __builtin_fmaf(p, f, 0x1.430912p-13f);
+  p = __builtin_fmaf(p, f, 0x1.5d87fep-10f);
+  p = __builtin_fmaf(p, f, 0x1.3b2ab6p-7f);
+  p = __builtin_fmaf(p, f, 0x1.c6b08ep-5f);
+  p = __builtin_fmaf(p, f, 0x1.ebfbep-3f);
+  p = __builtin_fmaf(p, f, 0x1.62e43p-1f);
+  p = __builtin_fmaf(p, f, 1.0f);
+  return __builtin_ldexpf(p, (int)n);
+}
+
 // SiLU z * sigmoid(z) = z / (1 + exp(-z)), correctly rounded division.
 __device__ __forceinline__ float silu_f32(float z) {
   float e = exp_f32(-z);

@@ -188,25 +188,6 @@ __device__ __forceinline__ float pass_max(const float (&v)[64]) {
   return m;
 }
 
-// exp_f32 for x <= 0 or NaN (every x_j - max): the same steps and bits; the
-// upper clamp is never reached, and the lower one as a select lets a NaN
-// through the polynomial by itself.
-__device__ __forceinline__ float exp_nonpos(float x_in) {
-  const float x = x_in < -104.0f ? -104.0f : x_in;
-  const float n = __builtin_rintf(x * 0x1.715476p+0f);
-  float r = __builtin_fmaf(-n, 0x1.62e4p-1f, x);
-  r = __builtin_fmaf(-n, 0x1.7f7d1cp-20f, r);
-  float p = 0x1.a01a02p-13f;
-  p = __builtin_fmaf(p, r, 0x1.6c16c2p-10f);
-  p = __builtin_fmaf(p, r, 0x1.111112p-7f);
-  p = __builtin_fmaf(p, r, 0x1.555556p-5f);
-  p = __builtin_fmaf(p, r, 0x1.555556p-3f);
-  p = __builtin_fmaf(p, r, 0.5f);
-  p = __builtin_fmaf(p, r, 1.0f);
-  p = __builtin_fmaf(p, r, 1.0f);
-  return __builtin_ldexpf(p, (int)n);
-}
-
 // Scale a pass and store it: y = v rinv, optionally rounded to bf16, times w,
 // plus b.
 template <int W, bool NORM>

@@ -1,6 +1,8 @@
-"""The library's device exp and SiLU (the functions the fused epilogue and
-the softmax kernels call) and exp2 (the attention kernel's) against the CPU
-oracle's dgo_exp / dgo_silu / dgo_exp2 on every binary32 input, bit for bit (NaNs compared as a class).  The exp is
+"""The library's device exp and SiLU (the fused epilogue, the one-wave
+softmax kernels) and exp2 (the chained attention kernel) against the CPU
+oracle's dgo_exp / dgo_silu / dgo_exp2 on every binary32 input, bit for bit
+(NaNs compared as a class), and exp_nonpos and exp2_nonpos (the other softmax
+and attention kernels) against those on every non-positive input and NaN.  The exp is
 the library's own fixed sequence of steps (Cody-Waite reduction, degree-7
 Taylor polynomial, exact power-of-two scaling), so its bits have no external
 reference: the oracle's plain C version of the same steps is what fixes
@@ -29,6 +31,8 @@ def probe():
     L.math_probe_exp_silu.restype = ctypes.c_int
     L.math_probe_exp2.argtypes = [ctypes.c_uint64, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p]
     L.math_probe_exp2.restype = ctypes.c_int
+    L.math_probe_nonpos.argtypes = [ctypes.c_uint64, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p]
+    L.math_probe_nonpos.restype = ctypes.c_int
     return L
 
 
@@ -78,3 +82,16 @@ def test_exp2_equals_the_oracle_on_every_binary32(probe, half):
             raise AssertionError("exp2 differs on %d inputs of slab 0x%08x; first bits 0x%08x: device %r, oracle %r"
                                  % (int((~ok).sum()), start, start + i, got[i], want[i]))
         print("exp2 slab 0x%08x ok" % start, flush=True)
+
+
+def test_nonpositive_versions_equal_the_general_ones(probe):
+    """-0 to -inf and the NaNs behind it, +0, and the positive NaNs."""
+    import torch
+    bad = torch.tensor([0, 0, -1, -1], dtype=torch.int32, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    for start, count in ((0, 1), (0x7F800001, 0x7FFFFF), (1 << 31, 1 << 31)):
+        assert probe.math_probe_nonpos(start, count, bad.data_ptr(), stream) == 0
+    torch.cuda.synchronize()
+    n = bad.cpu().numpy().view(np.uint32)
+    assert n[0] == 0 and n[1] == 0, "exp_nonpos differs on %d inputs from 0x%08x, exp2_nonpos on %d from 0x%08x" % (
+        n[0], n[2], n[1], n[3])
