@@ -87,7 +87,7 @@ hipError_t launch_gemm_odd(const GemmArgs& a, int kern, int tm, int tn, hipStrea
     if (tm == 32 && tn == 64) return launch_skinny_o<2, 64, 2, 256>(a, st);
   }
   if (kern == 3) return launch_v3_o<64, 128, 2, 2, 64>(a, st);
-  if (kern == 5) return tm == 256 ? launch_pp_o<256, 256, 32>(a, st) : launch_pp_o<128, 128, 64>(a, st);
+  if (kern == 5) return launch_pp_o<256, 256, 32>(a, st);
   return hipErrorInvalidValue;
 }
 

@@ -73,7 +73,8 @@ def test_odd_sizes(dg, di, shape):
 
 @pytest.mark.parametrize("shape", [(1030, 1537, 77), (2049, 4097, 33), (3000, 4099, 40)])
 def test_odd_sizes_wide(dg, shape):
-    """The ping-pong blocks (128 and 256 wide) at odd sizes, column sums of the output included."""
+    """The ping-pong kernel's 256 x 256 blocks at odd sizes, column sums of the
+    output included, and (1030 x 1537) the ring beside its own column-sum launch."""
     import torch
     M, N, K = shape
     A, B = inputs.spread_bf16(M, (M, K)), inputs.spread_bf16(N, (K, N))
