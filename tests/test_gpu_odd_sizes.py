@@ -122,3 +122,32 @@ def test_odd_short_parts(dg, di, shape):
     torch.cuda.synchronize()
     rows = np.unique(np.r_[0:min(M, 70), M // 2, M - 66 if M > 66 else 0:M])
     assert_bits_equal(host_bits(C)[rows], oracle.gemm(desc, np.ascontiguousarray(A[rows]), B, bias), "%s %s" % (shape, desc))
+
+
+@pytest.mark.parametrize("M,dtype", [(1, "bf16"), (33, "f16"), (130, "bf16")])
+def test_odd_past_31_bits(dg, M, dtype):
+    """A weight so wide that 66 of its rows pass 31-bit offsets: the few-row and
+    transposing-read kernels with chunks loaded where they lie, against the
+    generic kernel on every output and the oracle on the first and last columns."""
+    import torch
+    K, N = 9, 16268817
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    g = torch.Generator(device="cuda").manual_seed(M)
+
+    def operand(rows, cols):
+        buf = torch.full((rows * cols + 9,), float("nan"), dtype=dt, device="cuda")
+        buf[1:1 + rows * cols] = torch.randn(rows * cols, generator=g, device="cuda", dtype=torch.float32).to(dt)
+        return buf[1:1 + rows * cols].view(rows, cols)
+
+    print("M %d %s" % (M, dtype), flush=True)
+    A, B, bias = operand(M, K), operand(K, N), torch.randn(N, generator=g, device="cuda").to(torch.bfloat16)
+    desc = dict(tile_k=32, in_dtype=dtype, out="bf16", epilogue="bias")
+    C = [torch.zeros((M, N), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    dg.dg_gemm(dg.Desc(**desc), A, B, bias, C[0])
+    dg.dg_gemm(dg.Desc(**desc), A, B, bias, C[1], knobs=dict(kernel=1))
+    torch.cuda.synchronize()
+    assert torch.equal(C[0].view(torch.int16), C[1].view(torch.int16))
+    for cols in (slice(0, 128), slice(N - 77, N)):
+        a, b, z, c = (x.contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
+                      for x in (A, B[:, cols], bias[cols], C[0][:, cols]))
+        assert_bits_equal(c, oracle.gemm(desc, a, b, z), "M %d columns %s" % (M, cols))
