@@ -210,8 +210,9 @@ __device__ __forceinline__ char* split_slot() {
 // A wave alone on its SIMD issues one instruction every four cycles or more,
 // so the loop is bound by instructions, not only by its chain: unmasked, the
 // blocks past the end need no test (their V rows and records lie past the
-// resources' ends and read as zeros), and every address is a lane constant
-// plus one scalar that advances a block.
+// resources' ends and read as zeros: the range check counts the scalar offset
+// too, as measured within one allocation), and every address is a lane
+// constant plus one scalar that advances a block.
 template <int D, int W, int RD, bool CAUSAL>
 __global__ __launch_bounds__(64) void attn_split_out(SplitArgs s) {
   constexpr int NK = W / 32, ND = D / 16, RF = rec_floats<W>(), PER = 2 * NK + 2;
@@ -356,9 +357,11 @@ bool attn_split_ok(const AttnArgs& a, int64_t dim, int key_block) {
   const int64_t tiles = a.H * ((a.Lq + 15) / 16);
   const bool fits = tiles <= 64 || (tiles <= 128 && (a.H <= 2 || (a.H <= 32 && a.Lk >= 2048))) ||
                     (tiles <= 256 && a.H <= 2 && a.Lk >= 2048);
-  // V's rows and a tile's records, eight blocks past the end included, within 31-bit offsets
-  return fits && (a.Lk + 9 * key_block) * dim * 2 <= 0x7fffffff &&
-         (split_records(a, key_block) + 9) * (16 * key_block + 48) * 4 <= 0x7fffffff &&
+  // V's rows and a tile's records within 31-bit offsets, with what attn_split_out
+  // asks for past the end: its steps run to a whole ring and each loads a ring
+  // further, 2 RD - 1 blocks (RD at most 8) and the offsets within a block
+  return fits && (a.Lk + 16 * key_block) * dim * 2 <= 0x7fffffff &&
+         (split_records(a, key_block) + 16) * (16 * key_block + 48) * 4 <= 0x7fffffff &&
          attn_split_bytes(a, key_block) <= (256u << 20);
 }
 

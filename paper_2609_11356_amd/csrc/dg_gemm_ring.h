@@ -8,9 +8,9 @@
 // kernel (two slabs ahead through registers, LDS writes, a barrier between)
 // took 1150 cycles per 64-k slab of a 64 x 128 block however few MFMAs it
 // held; the ping-pong kernel 1400 per slab of 128 x 128 (512 of MFMA).  Here
-// a slab's loads have no register or LDS-write stage, two to five slabs are
-// in flight, and the wave reads the next 16-k step's fragments while it issues
-// the MFMAs of this one.  One barrier per slab, before its last step:
+// a slab's loads have no register or LDS-write stage, three slabs (of four
+// slots) or four (of five) are in flight, and the wave reads the next 16-k
+// step's fragments while it issues the MFMAs of this one.  One barrier per slab, before its last step:
 //   wait until the wave's own loads of slab s + 1 have landed, barrier; then
 //   the fragments of slab s + 1 may be read (every wave's loads of it are
 //   in), and the slot of slab s - 1 may be filled again (every wave has
@@ -55,8 +55,9 @@ typedef int intx2 __attribute__((ext_vector_type(2)));
 typedef int intx8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) intx2* lds_i2;
 
-// LDS array number ID of the workgroup (one per slot and operand, so that the
-// compiler can tell a read from the loads in flight).
+// LDS array number ID of the workgroup (one per slot, A's slab and then B's, so
+// that the compiler can tell a read of one slot from the loads in flight to
+// the others).
 template <int ID, int BYTES>
 __device__ __forceinline__ uint16_t* ring_array() {
   __shared__ __attribute__((aligned(1024))) uint16_t L[BYTES / 2];
