@@ -33,8 +33,9 @@
  *     one handle for a stream of every host thread, a call allocates and frees
  *     its own in stream order instead.  A stream may be destroyed only when its
  *     work is done, as a later stream can get the same handle.  A captured call
- *     keeps the workspace it found; the graph must not be replayed after a call
- *     on that stream that needs a larger one (dg_gemm_noalloc never does).
+ *     keeps the workspace it found, so a call of its size must have run on the
+ *     stream before, and the graph must not be replayed after one that needs
+ *     more (dg_gemm_noalloc, and calls that take no workspace, never do).
  */
 #ifndef DG_H
 #define DG_H
@@ -300,9 +301,10 @@ dg_status dg_gemm_colsum(const dg_desc* d, const void* A, const void* B, const v
                          void* C, float* colsum, int64_t M, int64_t N, int64_t K, void* stream);
 
 /* Sizes and alignment (dg_gemm): bf16 and binary16 operands run on the tiled
- * kernels at any N, K >= 8, any part start and any element-aligned pointers;
- * strided splits, scalar descriptors and a short leading tile off the chunk
- * grid keep the kernels named below. */
+ * kernels at any N, K >= 8, any part start and any element-aligned pointers
+ * (small products off the 8-element grid whose parts are one slab, on the
+ * generic kernel); strided splits, scalar descriptors and a short leading tile
+ * off the chunk grid keep the kernels named below. */
 
 /* Speed knobs for dg_gemm_knobs.  Any value gives the same bits as
  * dg_gemm; they exist so that this can be checked.  0 = the library's
@@ -334,9 +336,11 @@ typedef struct {
                       on 32-k steps from its start, fma = 0 only with the
                       16x16x32 instruction, a tree part at most 128 tiles,
                       otherwise DG_ERR_UNSUPPORTED; the library's choice
-                      there for fma = 0, while for fma = 1 kernel 0 runs
-                      smaller blocks that have no knob, on any size of at
-                      least 8 and any alignment and up to 256 tiles).  Binary16 operands
+                      there for fma = 0, and for fma = 1 where a tree of nine
+                      to sixteen tiles takes fewer rounds of the chip on it;
+                      else kernel 0 runs smaller blocks that have no knob, on
+                      any size of at least 8 and any alignment and up to 256
+                      tiles).  Binary16 operands
                       (in_dtype = DG_IN_F16) run on kernels 0, 1, 3, 4, 5, 6,
                       9 and 12; kernels 2, 7, 8 and 10 return DG_ERR_UNSUPPORTED.
                       An e4m3 B (DG_IN_BF16_E4M3) runs on kernel 1 (row-major)
@@ -413,8 +417,8 @@ dg_status dg_rowsum(const dg_desc* d, const float* X, float* out, int64_t rows,
  * run (the paper's evaluation, Sec. 7: rmsnorm).
  *   X: device, rows x cols fp32 row-major;  w: device, cols bf16 or NULL;
  *   Y: device, rows x cols of out_dtype (written, never read; may not
- *   overlap X).  rows = 0 or cols = 0 is a no-op.  One launch, or two on
- *   `stream` through a library-owned workspace of rows fp32 values per
+ *   overlap X).  rows = 0 or cols = 0 is a no-op.  One launch (always under
+ *   capture where one can serve the order), or two on `stream` through a library-owned workspace of rows fp32 values per
  *   (device, stream) (DG_ERR_NOMEM if it cannot grow).  Errors as dg_rowsum, plus
  *   DG_ERR_INVALID for a descriptor whose reduce_op is not DG_OP_SUMSQ. */
 dg_status dg_rmsnorm(const dg_desc* d, const float* X, const void* w, float eps, void* Y,
@@ -433,9 +437,9 @@ dg_status dg_rmsnorm(const dg_desc* d, const float* X, const void* w, float eps,
  * kernels (Sec. 7); the two sums are the order-sensitive steps.
  *   X: device, rows x cols fp32;  Y: device, rows x cols of out_dtype (may
  *   not overlap X).  rows = 0 or cols = 0 is a no-op.  One launch for
- *   contiguous leaves of 64 with fma = 1 and for strided lanes (64, 128 or
- *   256; 64 lanes past 65536 columns only below 512 rows); otherwise four
- *   launches through a library-owned workspace of rows x (cols + 2) fp32
+ *   contiguous leaves of 64 and strided lanes (64, 128 or 256) with fma = 1
+ *   where that is the faster way, under capture, or where the other way would
+ *   hold over 256 MB, up to 8388608 columns; otherwise four launches through a library-owned workspace of rows x (cols + 2) fp32
  *   values per (device, stream).  Errors as dg_rowsum. */
 dg_status dg_layernorm(const dg_desc* d, const float* X, const void* w, const void* b, float eps,
                        void* Y, int64_t rows, int64_t cols, void* stream);
@@ -453,11 +457,12 @@ dg_status dg_layernorm(const dg_desc* d, const float* X, const void* w, const vo
  *   X: device, rows x cols fp32 row-major;  Y: device, rows x cols of
  *   out_dtype (written, never read; may not overlap X).  rows = 0 or
  *   cols = 0 is a no-op.  One launch when the descriptor has contiguous
- *   leaves of 64 or strided lanes (64, 128 or 256); fewer than 256 rows of
- *   65537 to 262144 columns over contiguous leaves take three launches and a
- *   small workspace, any other descriptor three launches through a
- *   library-owned workspace of rows x (cols + 1) fp32 values per (device,
- *   stream) (DG_ERR_NOMEM if it cannot grow).  Errors as dg_rowsum, plus DG_ERR_INVALID for a
+ *   leaves of 64 or strided lanes (64, 128 or 256) where that is the faster
+ *   way, under capture, or where the other way would hold over 256 MB, up to
+ *   8388608 columns; fewer than 256 rows of 65537 to 262144 columns
+ *   over contiguous leaves take three launches and a small workspace, anything
+ *   else three launches through a library-owned workspace of rows x (cols + 1)
+ *   fp32 values per (device, stream) (DG_ERR_NOMEM if it cannot grow).  Errors as dg_rowsum, plus DG_ERR_INVALID for a
  *   descriptor whose reduce_op is not DG_OP_SUM. */
 dg_status dg_softmax(const dg_desc* d, const float* X, void* Y, int64_t rows, int64_t cols,
                      void* stream);

@@ -976,7 +976,15 @@ static dg::RowsumArgs rowsum_args(const dg_desc* d, const float* X, float* out, 
 // 224 us).
 static bool rowsum_over_waves(const dg::RowsumArgs& a) {
   if (!(a.rows < 1024 && a.cols > 8192) && (a.strided || (a.cols % 4 == 0 && aligned(a.X, 16)))) return false;
-  return dg::row_fused_ok(a, dg::ROW_SUM, a.rows, a.cols, cu_count());
+  return dg::row_fused_can(a, dg::ROW_SUM, a.cols) && dg::row_fused_pays(a, dg::ROW_SUM, a.rows, a.cols, cu_count());
+}
+
+// Whether a normalisation takes the one launch without a workspace that can
+// serve it: where that is the faster way, where the others would hold more
+// than 256 MB for their speed, and under capture, where a workspace would have
+// to be there already.
+static bool prefers_row_fused(const dg::RowsumArgs& a, int kind, int64_t rows, int64_t cols, size_t ws, hipStream_t st) {
+  return dg::row_fused_pays(a, kind, rows, cols, cu_count()) || ws > ((size_t)256 << 20) || capturing(st);
 }
 
 dg_status dg_rowsum(const dg_desc* d, const float* X, float* out, int64_t rows, int64_t cols,
@@ -1030,14 +1038,16 @@ dg_status dg_softmax(const dg_desc* d, const float* X, void* Y, int64_t rows, in
     if (dg::launch_softmax_split(n, (float*)ws, st) != hipSuccess) return DG_ERR_HIP;
     return DG_OK;
   }
-  if (dg::row_fused_ok(a, dg::ROW_SMX, rows, cols, cu_count())) {
-    if (dg::launch_row_fused(a, n, dg::ROW_SMX, st) != hipSuccess) return DG_ERR_HIP;
-    return DG_OK;
-  }
+  const size_t ws_bytes = (size_t)rows * (size_t)(cols + 1) * sizeof(float);
+  const bool one_launch = dg::row_fused_can(a, dg::ROW_SMX, cols);
+  if (one_launch && prefers_row_fused(a, dg::ROW_SMX, rows, cols, ws_bytes, st))
+    return dg::launch_row_fused(a, n, dg::ROW_SMX, st) == hipSuccess ? DG_OK : DG_ERR_HIP;
   // exponentials to the workspace, their reciprocal sums after them, then the products
   void* ws = nullptr;
   Lease lease;
-  dg_status s = get_workspace(st, (size_t)rows * (size_t)(cols + 1) * sizeof(float), &ws, &lease);
+  dg_status s = get_workspace(st, ws_bytes, &ws, &lease);
+  if (s == DG_ERR_NOMEM && one_launch)
+    return dg::launch_row_fused(a, n, dg::ROW_SMX, st) == hipSuccess ? DG_OK : DG_ERR_HIP;
   if (s != DG_OK) return s;
   float* E = (float*)ws;
   float* rinv = E + rows * cols;
@@ -1082,14 +1092,16 @@ dg_status dg_layernorm(const dg_desc* d, const float* X, const void* w, const vo
     if (dg::launch_layernorm_fused(a, n, st) != hipSuccess) return DG_ERR_HIP;
     return DG_OK;
   }
-  if (dg::row_fused_ok(a, dg::ROW_LN, rows, cols, cu_count())) {
-    if (dg::launch_row_fused(a, n, dg::ROW_LN, st) != hipSuccess) return DG_ERR_HIP;
-    return DG_OK;
-  }
+  const size_t ws_bytes = (size_t)rows * (size_t)(cols + 2) * sizeof(float);
+  const bool one_launch = dg::row_fused_can(a, dg::ROW_LN, cols);
+  if (one_launch && prefers_row_fused(a, dg::ROW_LN, rows, cols, ws_bytes, st))
+    return dg::launch_row_fused(a, n, dg::ROW_LN, st) == hipSuccess ? DG_OK : DG_ERR_HIP;
   // means, centred values, reciprocal roots, then the scaling
   void* ws = nullptr;
   Lease lease;
-  dg_status s = get_workspace(st, (size_t)rows * (size_t)(cols + 2) * sizeof(float), &ws, &lease);
+  dg_status s = get_workspace(st, ws_bytes, &ws, &lease);
+  if (s == DG_ERR_NOMEM && one_launch)
+    return dg::launch_row_fused(a, n, dg::ROW_LN, st) == hipSuccess ? DG_OK : DG_ERR_HIP;
   if (s != DG_OK) return s;
   float* D = (float*)ws;
   float* mean = D + rows * cols;
@@ -1142,13 +1154,15 @@ dg_status dg_rmsnorm(const dg_desc* d, const float* X, const void* w, float eps,
     if (dg::launch_rmsnorm_fused(a, n, st) != hipSuccess) return DG_ERR_HIP;
     return DG_OK;
   }
-  if (dg::row_fused_ok(a, dg::ROW_RMS, rows, cols, cu_count())) {
-    if (dg::launch_row_fused(a, n, dg::ROW_RMS, st) != hipSuccess) return DG_ERR_HIP;
-    return DG_OK;
-  }
+  const size_t ws_bytes = (size_t)rows * sizeof(float);
+  const bool one_launch = dg::row_fused_can(a, dg::ROW_RMS, cols);
+  if (one_launch && prefers_row_fused(a, dg::ROW_RMS, rows, cols, ws_bytes, st))
+    return dg::launch_row_fused(a, n, dg::ROW_RMS, st) == hipSuccess ? DG_OK : DG_ERR_HIP;
   void* ws = nullptr;
   Lease lease;
-  dg_status s = get_workspace(st, (size_t)rows * sizeof(float), &ws, &lease);
+  dg_status s = get_workspace(st, ws_bytes, &ws, &lease);
+  if (s == DG_ERR_NOMEM && one_launch)
+    return dg::launch_row_fused(a, n, dg::ROW_RMS, st) == hipSuccess ? DG_OK : DG_ERR_HIP;
   if (s != DG_OK) return s;
   a.out = (float*)ws;
   n.rinv = (const float*)ws;

@@ -174,7 +174,8 @@ hipError_t launch_layernorm_center(const NormArgs& a, hipStream_t s);
 // one pass with the row in registers over the waves of a workgroup (dg_rownorm.hip):
 // rowsum into r.out, RMS norm, layer norm or softmax into a.Y (r.eps the norms' eps)
 enum { ROW_SUM = 0, ROW_RMS = 1, ROW_LN = 2, ROW_SMX = 3 };
-bool row_fused_ok(const RowsumArgs& r, int kind, int64_t rows, int64_t cols, int ncu);
+bool row_fused_can(const RowsumArgs& r, int kind, int64_t cols);
+bool row_fused_pays(const RowsumArgs& r, int kind, int64_t rows, int64_t cols, int ncu);   // where it can
 hipError_t launch_row_fused(const RowsumArgs& r, const NormArgs& a, int kind, hipStream_t s);
 // softmax of few wide rows over many workgroups per row, through ws
 bool softmax_split_ok(const RowsumArgs& r, int64_t rows, int64_t cols);

@@ -24,7 +24,7 @@
 //
 // Measured on MI355X (host-timed back to back, bf16 out) against the two to
 // four passes through a workspace, which stay where they are the faster
-// (row_fused_ok): layer norm 4096 x 4096
+// (row_fused_pays): layer norm 4096 x 4096
 // 25.1 us (4.0 TB/s) from 82.8, 64 x 32768 12.3 from 107; softmax 4096 x 16384
 // 93 us (4.3 TB/s) from 314, 64 x 100000 26 from 322; RMS norm 16384 x 4096
 // 100 us from 127; row sums of 64 x 32768 7.7 us from 18.6.
@@ -451,22 +451,25 @@ extern template hipError_t launch_row_fused_w<64>(const RowsumArgs&, const NormA
 extern template hipError_t launch_row_fused_w<128>(const RowsumArgs&, const NormArgs&, int, hipStream_t);
 extern template hipError_t launch_row_fused_w<256>(const RowsumArgs&, const NormArgs&, int, hipStream_t);
 
-// Whether a call runs here (speed only: the kernels of dg_rowsum.hip, one wave
-// per row in one to four launches, give the same bits).  Contiguous leaves of
-// 64 or 64, 128, 256 strided lanes, any alignment and length up to the pass
-// roots LDS holds; squares by the fused square-add.
-//
-// Where both can run, the lines below are where the two cross on MI355X
-// (operands from HBM, bf16 out, us, one wave a row -> here).  A row of np
-// passes holds the 1, 4 or 16 waves it is built for whatever np is, and over
-// strided lanes the waves fold in turn, so the cost here is per row and round
-// of the chip (256 rows of 5 to 16 passes, or of more); there it is per
-// element, and several times higher where a row starts off the vector loads
-// (`al` false).
-bool row_fused_ok(const RowsumArgs& r, int kind, int64_t rows, int64_t cols, int ncu) {
+// Whether a call can run here: contiguous leaves of 64 or 64, 128, 256 strided
+// lanes, any alignment and length up to the pass roots LDS holds; squares by
+// the fused square-add.
+bool row_fused_can(const RowsumArgs& r, int kind, int64_t cols) {
   if (cols < 1 || cols > (int64_t)MAX_PASSES * PASS) return false;
   if ((kind == ROW_RMS || kind == ROW_LN || r.sumsq) && !r.fma) return false;
-  if (r.strided ? (r.leaf_w != 64 && r.leaf_w != 128 && r.leaf_w != 256) : r.leaf_w != 64) return false;
+  return r.strided ? (r.leaf_w == 64 || r.leaf_w == 128 || r.leaf_w == 256) : r.leaf_w == 64;
+}
+
+// Whether one that can should (speed only: the kernels of dg_rowsum.hip, one
+// wave per row in one to four launches, give the same bits).
+//
+// The lines below are where the two cross on MI355X (operands from HBM, bf16
+// out, us, one wave a row -> here).  A row of np passes holds the 1, 4 or 16
+// waves it is built for whatever np is, and over strided lanes the waves fold
+// in turn, so the cost here is per row and round of the chip (256 rows of 5 to
+// 16 passes, or of more); there it is per element, and several times higher
+// where a row starts off the vector loads (`al` false).
+bool row_fused_pays(const RowsumArgs& r, int kind, int64_t rows, int64_t cols, int ncu) {
   const int64_t np = (cols + PASS - 1) / PASS, rounds = (rows + ncu - 1) / ncu;
   const bool al = cols % 4 == 0 && ((uintptr_t)r.X & 15) == 0, full = cols % PASS == 0;
   const int W = r.strided ? r.leaf_w : 0;
@@ -508,8 +511,9 @@ bool row_fused_ok(const RowsumArgs& r, int kind, int64_t rows, int64_t cols, int
   }
   // RMS norm: two launches there.  64 lanes: 128 x 32768 40 -> 30, 512 x 32768 53
   // -> 64, 1000 x 20000 42 -> 99, 500 x 32769 93 -> 63; 128 lanes: 256 x 20000 27 ->
-  // 19, 1000 x 20000 42 -> 65, 1000 x 32769 113 -> 96; 256 lanes: 500 x 20000 29 ->
-  // 26, 1000 x 20000 41 -> 49, 1000 x 32768 65 -> 62
+  // 19, 1000 x 20000 42 -> 65, 1000 x 32769 113 -> 96, 2000 x 16385 89 -> 101, 4175 x
+  // 16499 224 -> 207; 256 lanes: 500 x 20000 29 -> 26, 1000 x 20000 41 -> 49, 1000 x
+  // 32768 65 -> 62
   if (np > 16) {
     if (!al) return true;
     return W == 64 ? rows <= 32 : rounds <= 1 || (W == 256 && np >= 21);
@@ -518,7 +522,7 @@ bool row_fused_ok(const RowsumArgs& r, int kind, int64_t rows, int64_t cols, int
     if (W == 64) return !al || (full && rows > 1 && rounds <= 4);
     return !(al && W == 128 && rows < 4);
   }
-  if (!al) return W == 64 ? rounds <= (np <= 8 ? 2 : 3) : W == 128 ? rounds <= 3 || np > 8 : true;
+  if (!al) return W == 64 ? rounds <= (np <= 8 ? 2 : 3) : W == 128 ? rounds <= 3 || np > 8 || (np == 5 && rounds > 10) : true;
   if (W == 64) return (rounds <= 1 && (rows > 1 || np > 5)) || (rounds == 2 && np >= 12);
   if (W == 128) return rounds <= 1 || (rounds == 2 && (full || np > 8)) || np >= 12;
   return rounds <= 2 || np >= 8;

@@ -88,7 +88,7 @@ def test_softmax_special_rows(dg, cols):
     assert torch.isnan(Y[1:4]).all() and not torch.isnan(Y[0]).any() and not torch.isnan(Y[4]).any()
 
 
-# both sides of each line at which row_fused_ok hands a call to the one-wave
+# both sides of each line at which row_fused_pays hands a call to the one-wave
 # kernels: (operation, leaf order, rows, cols)
 LINES = [("rmsnorm", 0, 256, 640), ("rmsnorm", 0, 257, 640), ("rmsnorm", 0, 2049, 640), ("rmsnorm", 0, 4, 2052),
          ("rmsnorm", 0, 5, 2052), ("rmsnorm", 0, 513, 2052), ("rmsnorm", 1, 2048, 65), ("rmsnorm", 2, 2049, 65),
@@ -121,3 +121,45 @@ def test_lines_between_row_kernels(dg, op, oi, rows, cols):
         want = oracle.softmax(desc, X)
     torch.cuda.synchronize()
     assert_bits_equal(host_bits(got), want, "%s %s %d x %d" % (op, desc, rows, cols))
+
+
+@pytest.mark.parametrize("op,oi,rows,cols", [("rmsnorm", 2, 2100, 65), ("softmax", 2, 2100, 129), ("layernorm", 1, 4100, 129)])
+def test_captured_normalisation_takes_no_workspace(dg, op, oi, rows, cols):
+    """Calls that eagerly go through a workspace because that is faster: under
+    capture they take the launch that needs none, on a stream that has none,
+    and replay to the eager bits."""
+    import ctypes
+
+    import torch
+    desc = dict(ORDERS[oi], out="f32", reduce="sumsq" if op == "rmsnorm" else "sum")
+    X = dev_f32(inputs.lognormal_f32(rows + cols, (rows, cols), sigma=1.0))
+    d, got, want = dg.Desc(**desc), torch.zeros((rows, cols), device="cuda"), torch.zeros((rows, cols), device="cuda")
+
+    def call(Y):
+        if op == "rmsnorm":
+            dg.dg_rmsnorm(d, X, None, 1e-5, Y)
+        elif op == "layernorm":
+            dg.dg_layernorm(d, X, None, None, 1e-5, Y)
+        else:
+            dg.dg_softmax(d, X, Y)
+
+    print(op, desc, rows, cols, flush=True)
+    call(want)
+    torch.cuda.synchronize()
+    hip, raw = ctypes.CDLL("libamdhip64.so"), ctypes.c_void_p()
+    assert hip.hipStreamCreate(ctypes.byref(raw)) == 0
+    free = torch.cuda.mem_get_info()[0]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=torch.cuda.ExternalStream(raw.value)):
+        call(got)
+    for _ in range(3):
+        got.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+        call(want)
+    assert free - torch.cuda.mem_get_info()[0] < 64 << 20
+    del g
+    torch.cuda.synchronize()
+    assert hip.hipStreamDestroy(raw) == 0
