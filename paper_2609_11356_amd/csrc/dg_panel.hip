@@ -335,21 +335,22 @@ int panel_default_depth(int tms, bool b8) { return default_depth(tms, b8); }
 
 // The parts meet inside the kernel where they are two to eight contiguous
 // ones, at the library's own depth: no partials, no second launch (8 x 4096 x
-// 14336 in eight parts 25.3 -> 20.4 us, 1 x 1024 x 1024 in two 11.9 -> 6.3).
-// A workgroup then reads on one CU what its parts read on f where panels are
-// few (16 x 512 x 8192 in eight parts 11.75 us apart, 12.75 merged; 64 x 512 x
-// 14336 16.3 and 58; 64 x 1024 x 2048 in four 9.9 and 13.2; 48 x 3072 x 4096 in
-// three, f = 1.3, 22.3 and 19.6), so it must not be more than the second launch
-// saves: the share that others would read, squared, of some 155 KB with 16 rows
-// a wave, 77 with 32, 53 with 64.  Where panels are more than the CUs, S waves that end
-// together fill the last round worse than S waves of their own, by the empty
-// part of the round and about a tenth, which grows with K while what merging
-// saves (the launch, the partials written and read) does not: 64 x 5760 x 14336
-// in two parts 97.4 us apart, 128 merged; 64 x 5760 x 512 12.6 and 11.2; 64 x
-// 8192 x 14336 in eight 136 and 143, x 2048 41.0 and 30.1.  With the panels'
-// bytes at 16 TB/s (A's come from the caches) and the partials' at 4.2, the
-// estimate below takes the faster way, or one within 7 % of it, at 98 % of 4164
-// measured sizes (operands from HBM).
+// 14336 in eight parts 25.3 -> 20.4 us, 1 x 1024 x 1024 in two 11.9 -> 6.3). A
+// workgroup then reads on one CU what its parts read on f where panels are few
+// (16 x 512 x 8192 in eight parts 11.75 us apart, 12.75 merged; 64 x 512 x
+// 14336 16.3 and 58; 64 x 1024 x 2048 in four 9.9 and 13.2; 48 x 3072 x 4096
+// in three, f = 1.3, 22.3 and 19.6), so it must not be more than the second
+// launch saves: the share that others would read, squared, of some 155 KB with
+// 16 rows a wave, 77 with 32, 53 with 64.  Where panels are more than the CUs,
+// S waves that end together fill the last round worse than S waves of their
+// own, by the empty part of the round and about a tenth (up to 8 rows, which
+// wait for HBM, 3 %), which grows with K while what merging saves (the launch,
+// the partials written and read) does not: 64 x 5760 x 14336 in two parts 97.4
+// us apart, 128 merged; 64 x 5760 x 512 12.6 and 11.2; 64 x 8192 x 14336 in
+// eight 136 and 143, x 2048 41.0 and 30.1.  With the panels' bytes at 16 TB/s
+// (20 up to 8 rows; A's come from the caches) and the partials' at 4.2, the
+// estimate below takes the faster way, or one within 7 % of it, at 98 % of
+// 4164 measured sizes (operands from HBM).
 bool panel_merges(const GemmArgs& a, int tms, int depth, int ncu) {
   const bool b8 = a.b_e4m3 != 0;
   if (a.S < 2 || a.S > 8 || a.split_w != 0 || depth != default_depth(tms, b8)) return false;
@@ -361,8 +362,8 @@ bool panel_merges(const GemmArgs& a, int tms, int depth, int ncu) {
     return kb * apart * apart <= (tms == 1 ? 155 : tms == 2 ? 77 : 53) && runs * (1 + (b8 ? 2 : 1) * tms) * apart <= 250;
   }
   const double rounds = std::ceil(panels / ncu);
-  const double empty = rounds * ncu / panels - 1 + (panels > ncu ? 0.11 : 0);
-  return panels * kb * empty / 16000 <= 2.5 + 8.0 * a.S * (double)a.M * (double)a.N / 4.2e6;   // us
+  const double empty = rounds * ncu / panels - 1 + (panels > ncu ? (a.M <= 8 ? 0.03 : 0.11) : 0);
+  return panels * kb * empty / (a.M <= 8 ? 20000 : 16000) <= 2.5 + 8.0 * a.S * (double)a.M * (double)a.N / 4.2e6;   // us
 }
 
 template <int TMS, int D, bool AVEC>

@@ -509,17 +509,18 @@ bool row_fused_pays(const RowsumArgs& r, int kind, int64_t rows, int64_t cols, i
     if (rounds == 3 && W == 64 && np > 5) return true;
     return W < 256 && full;
   }
-  // RMS norm: two launches there.  64 lanes: 128 x 32768 40 -> 30, 512 x 32768 53
-  // -> 64, 1000 x 20000 42 -> 99, 500 x 32769 93 -> 63; 128 lanes: 256 x 20000 27 ->
-  // 19, 1000 x 20000 42 -> 65, 1000 x 32769 113 -> 96, 2000 x 16385 89 -> 101, 4175 x
-  // 16499 224 -> 207; 256 lanes: 500 x 20000 29 -> 26, 1000 x 20000 41 -> 49, 1000 x
-  // 32768 65 -> 62
+  // RMS norm: two launches there.  64 lanes: 128 x 32768 40 -> 30, 512 x 32768
+  // 53 -> 64, 1000 x 20000 42 -> 99, 500 x 32769 93 -> 63, 1000 x 8196 25 -> 31,
+  // 6000 x 8196 102 -> 93; 128 lanes: 256 x 20000 27 -> 19, 1000 x 20000 42 ->
+  // 65, 1000 x 32769 113 -> 96, 2000 x 16385 89 -> 101, 4175 x 16499 224 -> 207;
+  // 256 lanes: 500 x 20000 29 -> 26, 1000 x 20000 41 -> 49, 1000 x 32768 65 ->
+  // 62
   if (np > 16) {
     if (!al) return true;
     return W == 64 ? rows <= 32 : rounds <= 1 || (W == 256 && np >= 21);
   }
   if (np <= 4) {
-    if (W == 64) return !al || (full && rows > 1 && rounds <= 4);
+    if (W == 64) return !al || (full ? rows > 1 && rounds <= 4 : rounds > 20);
     return !(al && W == 128 && rows < 4);
   }
   if (!al) return W == 64 ? rounds <= (np <= 8 ? 2 : 3) : W == 128 ? rounds <= 3 || np > 8 || (np == 5 && rounds > 10) : true;
