@@ -335,7 +335,7 @@ int panel_default_depth(int tms, bool b8) { return default_depth(tms, b8); }
 
 // The parts meet inside the kernel where they are two to eight contiguous
 // ones, at the library's own depth: no partials, no second launch (8 x 4096 x
-// 14336 in eight parts 25.3 -> 20.4 us, 1 x 1024 x 1024 in two 11.9 -> 6.3). A
+// 14336 in eight parts 29.6 -> 23.9 us, 1 x 1024 x 1024 in two 11.9 -> 6.3). A
 // workgroup then reads on one CU what its parts read on f where panels are few
 // (16 x 512 x 8192 in eight parts 11.75 us apart, 12.75 merged; 64 x 512 x
 // 14336 16.3 and 58; 64 x 1024 x 2048 in four 9.9 and 13.2; 48 x 3072 x 4096
