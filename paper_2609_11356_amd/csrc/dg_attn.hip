@@ -17,7 +17,8 @@
 // (pv_fma) or from +0 and then added.  The end: O / l, or O * (1 / l).
 //
 // Two kernels: attn_fwd_t (below, tree row sums accumulated in place) and
-// attn_fwd, for the other orders and 16-row causal splits: one wave per RW
+// attn_fwd, for the other orders, 16-row causal splits and some short walks over
+// keys in blocks of 128 (rows_128): one wave per RW
 // query rows (16 or 32: one or two 16-row MFMA tiles), NW waves per workgroup (the rows of a workgroup share one causal
 // split: BLOCK_M is a multiple of RW NW).  Each block's K and V rows are in
 // LDS (two buffers: the next block's rows are fetched into registers while
@@ -642,6 +643,31 @@ hipError_t launch_t(const AttnArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Rows per wave of attn_fwd_t, or 0 where attn_fwd is the faster one, for
+// d = 128 and keys in blocks of 128 (speed only): attn_fwd_t's 128 KB of LDS
+// leave one workgroup per CU, attn_fwd's 80 KB two, so its overlap within a
+// workgroup has to make up for the second one.  Measured on MI355X, attn_fwd /
+// attn_fwd_t, operands from HBM, H heads of Lq x Lk:
+//   128-row workgroups (32-row waves) need more than one key block (2000 x 40
+//   0.76, 500 x 33 0.8, 128 x 128 0.93 to 1.04, 2000 x 200 0.96 to 1.09, 512 x
+//   512 1.3), and, where the last of them is half empty, keys enough for that
+//   too: 129 x 129 0.77, 257 x 257 0.9, 300 x 900 1.1 to 1.4, 130 x 1000 1.25
+//   (unmasked; causal at most 1.2, so half as many keys again: 400 x 400 0.97);
+//   64-row workgroups gain while each has a CU (H 256, 64 x 64 1.24; H 64,
+//   256 x 256 1.54), while two rounds of them stand against one of attn_fwd
+//   from two or three blocks of keys (H 384, 64 x 64 0.83; H 64, 257 x 257
+//   0.93, 300 x 900 1.17; causal H 128, 129 x 129 0.87, 256 x 256 1.10), and in
+//   more rounds on long keys only (causal H 512, 256 x 256 0.80, 640 x 640
+//   0.92; H 203, 1500 x 1500 1.02).
+int rows_128(const AttnArgs& a, bool rows32) {
+  constexpr int64_t ncu = 256;
+  const int64_t r64 = (a.Lq + 63) / 64, wg = a.H * r64;
+  const int64_t half = r64 % 2 ? (a.causal ? 2304 : 1536) / (r64 + 1) : 0;
+  if (rows32 && a.Lk > 128 + half) return 32;
+  if (wg <= ncu || a.Lk > 1024 || (wg <= 2 * ncu && a.Lk >= (a.causal ? 192 : 320))) return 16;
+  return 0;
+}
+
 // Workgroup shape of attn_fwd (speed only): 16-row waves (registers), eight of
 // them with the next block prefetched into a second buffer when the causal
 // split allows 128-row workgroups (four when it allows 64), else fewer waves
@@ -658,10 +684,14 @@ hipError_t launch_dw(const AttnArgs& a, hipStream_t st) {
   // offsets): 32-row waves once they fill the chip's 1024 SIMDs, else 16-row
   // ones, whose blocks take half the time
   if (a.block_tree && a.pv_fma && a.Lk * D * 2 <= 0x7fffffff) {
-    const bool full = a.H * ((a.Lq + 31) / 32) >= 1024;
-    if (bm % 128 == 0 && full) return launch_t<D, W, 4, 32>(a, st);
-    if (bm % 64 == 0) return launch_t<D, W, 4, 16>(a, st);
-    if (bm % 32 == 0) return launch_t<D, W, 2, 16>(a, st);
+    // (and where 128-key blocks leave room for few workgroups, rows enough that
+    // half of the waves aren't idle: d = 64, H 512, 64 x 64 12.8 -> 9.5 us)
+    const bool full = a.H * ((a.Lq + 31) / 32) >= 1024 && (W < 128 || a.Lq > 64);
+    int rows = bm % 128 == 0 && full ? 32 : 16;
+    if (W == 128 && D == 128 && bm % 64 == 0) rows = rows_128(a, rows == 32);
+    if (rows == 32) return launch_t<D, W, 4, 32>(a, st);
+    if (rows == 16 && bm % 64 == 0) return launch_t<D, W, 4, 16>(a, st);
+    if (bm % 64 && bm % 32 == 0) return launch_t<D, W, 2, 16>(a, st);
   }
   if constexpr (W == 128) {
     if (bm % 64 == 0) return launch_one<D, W, 4, 16, false>(a, st);

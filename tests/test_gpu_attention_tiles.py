@@ -203,3 +203,20 @@ def test_two_threads_on_the_per_thread_stream(dg):
     for _, _, _, _, _, wants, outs in work:
         for o, c in outs:
             assert torch.equal(o.view(torch.int16), wants[0].view(torch.int16)) and torch.equal(c, wants[1])
+
+
+@pytest.mark.parametrize("d,H,Lq,Lk,q_block", [
+    # keys in blocks of 128: one block in 128-row workgroups; more of them, the
+    # last half empty; 64-row workgroups in one round, two and more, few and long keys
+    (128, 256, 128, 128, 0), (128, 256, 128, 129, 0), (128, 256, 129, 512, 0), (128, 256, 129, 513, 0),
+    (128, 128, 416, 416, 128), (128, 128, 417, 417, 128), (128, 256, 64, 70, 0), (128, 257, 64, 319, 0),
+    (128, 257, 64, 320, 0), (128, 128, 191, 191, 64), (128, 128, 192, 192, 64), (128, 513, 33, 1024, 0),
+    (128, 513, 33, 1025, 0), (128, 171, 190, 190, 64), (64, 512, 64, 130, 0), (64, 512, 65, 130, 0)])
+def test_keys_in_blocks_of_128(dg, d, H, Lq, Lk, q_block):
+    desc = dict(key_block=128, causal=int(q_block > 0), q_block=q_block or 1, block_sum="tree", pv_fma=1, out="f32")
+    Q, K, V = qkv(Lq + Lk, H, Lq, Lk, d)
+    print("attention", H, Lq, Lk, d, q_block, flush=True)
+    got = run(dg, desc, Q, K, V, scale(d))
+    assert_bits_equal(got[:1], oracle.attention(desc, Q[:1], K[:1], V[:1], scale(d)), "%s %s" % (desc, (H, Lq, Lk, d)))
+    # heads are independent: the last one again, alone in a call
+    assert np.array_equal(run(dg, desc, Q[-1:], K[-1:], V[-1:], scale(d))[0], got[-1])
