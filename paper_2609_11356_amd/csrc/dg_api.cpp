@@ -638,14 +638,33 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
   // 128 x 64 blocks per CU, where the ring's one 64 x 128 block (eight levels)
   // takes so many more rounds: one of its rounds takes 1.6 of the ring's with
   // tiles of 32 (2048 x 8192 x 512 60.1 us, the ring 74.3; 617 x 8192 x 512 28.4,
-  // 27.5), nearly two with longer ones, which leaves it a ring's second round of
-  // few blocks (tile_k 256: 400 x 5696 x 4096, 315 of them, 65.6 and 76.1; 1500 x
-  // 2048 x 4096, 384, 67.2 and 60.9; 1000 x 5696 x 4096, 720, 121 and 103).
+  // 27.5; 512 x 2048 x 1536 in four parts, two rounds of the ring, 30.8 and 27.3),
+  // nearly two with longer ones, which leaves it a ring's second round of few
+  // blocks (tile_k 256: 400 x 5696 x 4096, 315 of them, 65.6 and 76.1; 1500 x 2048 x
+  // 4096, 384, 67.2 and 60.9; 1000 x 5696 x 4096, 720, 121 and 103).  From four
+  // rounds on, 1.6 or more of them to one, also where the XCDs' ranges of the
+  // ring's blocks serve it badly: block counts off a multiple of eight leave no
+  // ranges (tile_k 128: 1280 x 5696 x 2048, 900 blocks, 76.1 and 82.3; 1280 x 8192 x
+  // 2048, 1280, 98.7 and 91.1), and with block rows a power of two the XCDs walk
+  // the same columns in step (tile_k 64, 4096 x 8192 x 1024 167.9 and 207.5; 128,
+  // 2048 x 8192 x 1408 106.4 and 116.1; but 3072 x 8192 x 2048 211.8 and 203.4; 256,
+  // 8192 x 2048 x 4096 257.9 and 251.9, 4096 x 4096 x 4096 256.3 and 271.4).  From
+  // six rounds on, nearly two to one, with any tiles of 64 in 64 x 128 blocks (7168
+  // x 11008 x 576 254.2 and 275.7, 7168 x 8192 x 1024 287.7 and 291.3; 2500 x 5696 x
+  // 1024, 64 x 64 blocks, 81.0 and 77.0).
   bool ring_tiles = tc_ok && p.fma == 1 && (p.tile_combine != DG_TREE || part_tiles <= 256) && pp_fits(a);
   if (ring_tiles && p.tile_combine == DG_TREE && part_tiles > 8 && part_tiles <= 16) {
     const int64_t ncu = cu_count(), ring_blocks = a.S * ((M + 63) / 64) * ((N + 127) / 128);
     const int64_t rr = (ring_blocks + ncu - 1) / ncu, rt = (a.S * ((M + 127) / 128) * ((N + 63) / 64) + 2 * ncu - 1) / (2 * ncu);
-    if (p.tile_k <= 32 ? 5 * rr > 8 * rt : rr == 2 && rt == 1 && 20 * ring_blocks <= 27 * ncu) ring_tiles = false;
+    if (p.tile_k <= 32 ? 5 * rr > 8 * rt && (a.S == 1 || rr > 2) : rr == 2 && rt == 1 && 20 * ring_blocks <= 27 * ncu) ring_tiles = false;
+    if (rr >= 4 && 5 * rr >= 8 * rt) {
+      int bm, bn;
+      ring_config(M, N, a.S, ncu, true, false, &bm, &bn);
+      const int64_t rows = (M + bm - 1) / bm, blocks = rows * ((N + bn - 1) / bn);
+      if (blocks % 8 || (p.tile_k < 256 && (rows & (rows - 1)) == 0) ||
+          (p.tile_k < 128 && bn == 128 && rr >= 6 && 4 * rr > 7 * rt))
+        ring_tiles = false;
+    }
   }
   if (p.tile_combine == DG_TREE && part_tiles > 128) tc_ok = false;
   if (scalar) {

@@ -181,7 +181,8 @@ def test_few_rows(dg, M, N, K, S):
 # trees of nine to sixteen tiles, on both sides of the line between the ring and
 # the tile-combine kernel (rounds of the chip that each would take)
 TREES = [(400, 5696, 512, 32), (1000, 5696, 512, 32), (64, 5696, 512, 32), (2048, 2056, 288, 32), (400, 5696, 576, 64),
-         (1000, 5696, 1024, 64), (400, 5696, 2304, 256)]
+         (1000, 5696, 1024, 64), (400, 5696, 2304, 256), (1280, 5696, 576, 64), (1280, 8192, 576, 64),
+         (2000, 4096, 576, 64), (2000, 4096, 2304, 256), (6100, 2048, 576, 64), (1792, 8192, 576, 64)]
 
 
 @pytest.mark.parametrize("M,N,K,tile_k", TREES)
