@@ -261,8 +261,14 @@ void ring_config(int64_t M, int64_t N, int S, int ncu, bool tiles, bool big, int
 // blocks fetch the operands more often.  Operands from HBM, kernel 13 and the
 // ring: 2048 x 4096 x 4096 (256 blocks) 51.8 and 47.2 us, 1300 x 4096 x 4096
 // 43.5 and 40.0; 1001 x 10656 x 4096 (336) 66.4 and 77.6, 2048 x 6144 x 4096
-// (384) 68.2 and 71.5, 2048 x 10656 x 4096 (672) 121 and 149.
-bool ring_f8_config(int64_t M, int64_t N, int S, int ncu, int* tm, int* tn) {
+// (384) 68.2 and 71.5, 2048 x 10656 x 4096 (672) 121 and 149.  It also stays for
+// long parts where 128-row blocks are three, five or seven to a column and their
+// second round is begun in earnest: 640 x 7680 x 8192 (300 of them) 74.1 and 86.8,
+// 800 x 6144 x 8192 69.0 and 75.3, 300 x 12800 x 8192 74.8 and 87.4, 640 x 3840 x
+// 8192 in two parts 56.3 and 64.2 (640 x 6656 x 8192, 260 of them, 73.6 and 71.1;
+// four to a column 512 x 9600 x 8192 86.1 and 84.9, six 700 x 8192 x 8192 81.1 and
+// 74.7; 640 x 7680 x 2048 29.4 and 30.2).
+bool ring_f8_config(int64_t M, int64_t N, int64_t K, int S, int ncu, int* tm, int* tn) {
   auto rounds = [&](int64_t bm, int64_t bn, int64_t per) {
     return (double)((S * ((M + bm - 1) / bm) * ((N + bn - 1) / bn) + per - 1) / per);
   };
@@ -271,6 +277,8 @@ bool ring_f8_config(int64_t M, int64_t N, int S, int ncu, int* tm, int* tn) {
   const double c64 = rounds(64, 64, ncu) == 1 ? 13.5 : rounds(64, 64, 2 * ncu) * 20;
   if (std::min({c128, c64w, c64}) >= 38) return false;
   const bool b128 = c128 < c64w && c128 < c64;
+  const int64_t rows = (M + 127) / 128, blocks = S * rows * ((N + 127) / 128);
+  if (rows % 2 && rows >= 3 && rows <= 7 && K >= 4096 && K / S >= 2048 && 8 * blocks >= 9 * (int64_t)ncu) return false;
   *tm = b128 ? 128 : 64;
   *tn = b128 || c64w < c64 ? 128 : 64;
   return true;
@@ -578,7 +586,7 @@ static dg_status gemm_impl(const dg_desc* d, const void* A, const void* B, const
     if (kern == 13 && !f8_ok) return DG_ERR_UNSUPPORTED;
     if (kern == 0) kern = f8_ok ? 13 : 1;
     if (f8_ok && !(knobs && (knobs->kernel || tm || tn)) && M * K < 0x7fffffff && K * N < 0x7fffffff &&
-        ring_f8_config(M, N, a.S, cu_count(), &tm, &tn))
+        ring_f8_config(M, N, K, a.S, cu_count(), &tm, &tn))
       kern = RING_F8;
     // 256-row blocks (buffer offsets: M K and K N bytes below 2^31) from
     // 129 rows on, else 128 x 128

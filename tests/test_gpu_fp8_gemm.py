@@ -247,3 +247,17 @@ def test_other_entry_points(dg):
     want = oracle.gemm(dict(desc, in_dtype="e4m3"), A8, B8)
     assert_bits_equal(host_bits(C), want, "colsum GEMM")
     assert_bits_equal(cs.cpu().numpy(), oracle.colsum(want), "column sums")
+
+
+@pytest.mark.parametrize("M,N,K,S", [(300, 12160, 4096, 1), (300, 12288, 4096, 1), (640, 3840, 4096, 2), (640, 3840, 3968, 1),
+                                     (700, 6144, 4096, 1), (1100, 4096, 4096, 1)])
+def test_two_rounds_of_128_row_blocks(dg, M, N, K, S):
+    """Both sides of the line between the ring's 128 x 128 blocks and 256 x 128
+    ones: block rows odd and even, blocks and part length below and at it."""
+    desc = dict(mma="16x16x128_f8f6f4", tile_k=128, split_k=S, split_combine="tree")
+    A8, B8 = inputs.e4m3_uniform(M, (M, K)), inputs.e4m3_uniform(N, (K, N))
+    print("fp8", (M, N, K, S), flush=True)
+    got = run(dg, desc, A8, B8)
+    assert np.array_equal(got, run(dg, desc, A8, B8, knobs=dict(kernel=1)))
+    ii, jj = np.array([0, 127, 128, M // 2, M - 1] * 4), np.repeat([0, N // 2, N - 129, N - 1], 5)
+    assert_bits_equal(got[ii, jj], oracle.gemm_at(dict(desc, in_dtype="e4m3"), A8, B8, None, ii, jj), "%s" % ((M, N, K, S),))
